@@ -1,735 +1,710 @@
 // FP64 log|det|, sign and inverse of the Slater matrices (inversion step,
 // section "Overall performance of QMC=Chem"; Slater matrix D_ij = phi_i(r_j)).
 //
-// One workgroup inverts one n x n matrix held entirely in registers, by
-// Gauss-Jordan elimination with partial pivoting on the rows of D: at step k
-// the pivot is the largest |D[i][k]| over rows not yet used (smallest i on
-// exact ties; for 128 < n <= 224, among values within 2^-12 relative of
-// the largest, which leaves the elimination as stable).  Pivot rows are not
-// moved; the pivot sequence p_k is recorded and the result is un-permuted on
-// the way out: D^-1[k][p_j] = M[p_k][j].
+// One workgroup inverts one n x n matrix (n <= 224) held entirely in
+// registers, by Gauss-Jordan elimination with partial pivoting on the rows of
+// D: at step k the pivot is the largest |D[i][k]| over rows not yet used
+// (smallest i on exact ties; for n > 128, among values within 2^-12 relative
+// of the largest, which leaves the elimination as stable).  Pivot rows are
+// not moved; the pivot sequence p_k is recorded and the result is un-permuted
+// on the way out: D^-1[k][p_j] = M[p_k][j].
 // The pivots are the diagonal of U in P D = L U, so log|det| = sum log|pivot|
 // and sign = sign(permutation) prod sign(pivot).  2 n^3 flops per matrix.
+//
+// The rank-1 step of column k, with multipliers f_i = -D[i][k] / pv (0 in the
+// pivot row, which stays unscaled until the end): M[i][c] += f_i M[p_k][c],
+// and column k takes pv + 1 for its pivot-row entry, which turns it into
+// -D[i][k] / pv.  Steps are taken 16 columns (a panel) at a time without
+// changing a single rounding: one wave eliminates the panel, whose columns it
+// holds in its own registers (only lane exchanges inside a step), and
+// publishes the multipliers F of its steps; for every other column the
+// pivot-row entries w_k at step k come from those at the panel's start by
+// forward substitution (w_k += F_m[p_k] w_m, m < k ascending), and then
+// v += F w.  v_mfma_f64_16x16x4f64 adds its four products to the accumulator
+// one after the other in order, each with one rounding, as a chain of FMAs
+// does, so the updates on it give the rank-1 steps' values bit for bit.  A
+// panel's own column c is a column whose entries w_k with k <= c are 0.
+//
+// Layout: wave u of NU owns the D columns of tiles u and u + NU, 16 each, as
+// MFMA results (register row (lane / 16) + 4 r of a tile is D column e, lane
+// % 16 is D row i, so C_1[e][i], F and the panel are read and written in runs
+// of 16 values); the last wave is the panel wave.  Look-ahead: the wave
+// owning the next panel's columns updates that tile first and hands it over
+// in LDS, and the panel wave eliminates it while the others finish; one
+// barrier per panel publishes F.
+//
+// Bound: the panel wave's chain of search, reciprocal and update (about 800
+// cycles a step at n = 79, 1200 at n = 217), then the rank-16 updates at the
+// FP64 matrix rate (the same as the vector rate here).  Measured, against the
+// eight waves that published one or two rank-1 steps at a time through LDS
+// before: one matrix of n = 79 in 53 us (162), 2048 of them in 205 us (775),
+// 777 of n = 132 in 479 us (741), 2048 of n = 217 in 2.30 ms (2.61).
 #include <algorithm>
 
 #include "qsl_internal.h"
 
 namespace qsl {
 
+typedef __attribute__((ext_vector_type(4))) double f64x4;
+typedef __attribute__((ext_vector_type(2))) double f64x2;
 
-// Layout: wave v of NWV owns the D columns e = v + NWV c (c < CPW, electron
-// index), lane l owns the D rows i = l + 64 r (r < RPL, MO index); thread
-// (v, l) holds M[r][c] in registers, loaded coalesced from C_1[e][i].
-// Step k: the wave owning column k finds the pivot among the unused rows
-// (a wavefront argmax), publishes the column (zero in the pivot row) and
-// the pivot through LDS, one barrier; every wave then reads the pivot row
-// of its own columns from lane p % 64 with readlane (scalar registers) and
-// applies the rank-1 update.  The pivot row is left unscaled (it is divided
-// by its pivot on the way out), its column-k entry becomes 1; the other rows
-// of column k become -D[i][k]/pv through the entry 1 + 1/pv of the pivot row.
-
-// argmax of |col| over the unused rows of this lane, then over the wavefront
-// (largest value, smallest row index on exact ties): DPP exchanges inside
-// rows of 16 lanes (quad swaps, half-row and row mirrors), then the four row
-// results through scalar registers.  Publishes column and pivot.
-template <int RPL>
-__device__ __forceinline__ void gj_search(const double (&col)[RPL], int n, int lane, uint32_t used, double* colout,
-                                          int* piv_idx, double* piv_val) {
-    double best = -1.0;
-    int bi = 0x7fffffff;
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const int i = lane + 64 * r;
-        const double v = fabs(col[r]);
-        if (i < n && !((used >> r) & 1u) && v > best) { best = v; bi = i; }
-    }
-    argmax_step<0xB1>(best, bi);   // quad_perm [1,0,3,2]
-    argmax_step<0x4E>(best, bi);   // quad_perm [2,3,0,1]
-    argmax_step<0x141>(best, bi);  // row_half_mirror
-    argmax_step<0x140>(best, bi);  // row_mirror
-    double sb = readlane_f64(best, 0);
-    int si = __builtin_amdgcn_readlane(bi, 0);
-#pragma unroll
-    for (int rw = 1; rw < 4; ++rw) {
-        const double ob = readlane_f64(best, 16 * rw);
-        const int oi = __builtin_amdgcn_readlane(bi, 16 * rw);
-        if (ob > sb || (ob == sb && oi < si)) { sb = ob; si = oi; }
-    }
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const int i = lane + 64 * r;
-        if (i < n) colout[i] = (i == si) ? 0.0 : col[r];
-        if (i == si) *piv_val = col[r];
-    }
-    if (lane == 0) *piv_idx = si;
-}
-
-template <int NWV, int RPL, int CPW, typename Tin>
-__device__ __forceinline__ void gj_body(const Job& j, int bx) {
-    const Tin* __restrict__ C = (const Tin*)j.C;
-    const int n = j.n, spin = j.spin;
-    double* __restrict__ Dinv = j.Dinv;
-    double* __restrict__ logdet = j.logdet;
-    int8_t* __restrict__ sign = j.sign;
-    uint32_t* __restrict__ status = j.status;
-    constexpr int NT = NWV * 64;
-    constexpr int NR = 64 * RPL;   // capacity in D rows (MO index i)
-    constexpr int NC = NWV * CPW;  // capacity in D columns (electron index e)
-    constexpr int QC = 8;          // rows of D^-1 staged per output pass
-    __shared__ double colbuf[2][NR];
-    __shared__ int piv_idx[2];
-    __shared__ double piv_val[2];
-    __shared__ int perm[NC];
-    __shared__ int invp[NR];
-    __shared__ double rowpiv[NR];
-    __shared__ double stage[QC][NC > NR ? NC : NR];
-    __shared__ int s_flag;
-
-    const int w = bx;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
-    const size_t nn = (size_t)n * n;
-    const Tin* C1 = C + (size_t)w * 5 * nn;  // derivative 0 block
-
-    double M[RPL][CPW];
-#pragma unroll
-    for (int c = 0; c < CPW; ++c)
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            const int e = wave + NWV * c, i = lane + 64 * r;
-            M[r][c] = (e < n && i < n) ? (double)C1[(size_t)e * n + i] : 0.0;
-        }
-    for (int k = tid; k < NR; k += NT) { colbuf[0][k] = 0.0; colbuf[1][k] = 0.0; }
-    if (tid == 0) s_flag = 0;
-    __syncthreads();
-    uint32_t used = 0;  // bit r: row lane + 64 r already a pivot row
-    if (wave == 0) {
-        double col[RPL];
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) col[r] = M[r][0];
-        gj_search<RPL>(col, n, lane, used, colbuf[0], &piv_idx[0], &piv_val[0]);
-    }
-
-    bool singular = false;
-    for (int k = 0; k < n; ++k) {
-        const int b = k & 1;
-        __syncthreads();  // pivot and column k are published, step k-1 is done
-        const int p = __builtin_amdgcn_readfirstlane(piv_idx[b]);
-        const double pv = piv_val[b];
-        if (p >= n || !(pv != 0.0) || !isfinite(pv)) {  // zero (or NaN) pivot
-            singular = true;
-            if (tid == 0) s_flag = isfinite(pv) || p >= n ? 1 : 2;
-            break;
-        }
-        const double inv = 1.0 / pv;
-        const int lp = p & 63, rp = p >> 6;  // wave-uniform
-        const int vk = k % NWV, ck = k / NWV;
-        double colv[RPL];
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) colv[r] = colbuf[b][lane + 64 * r];
-        if (tid == 0) {
-            perm[k] = p;
-            rowpiv[p] = pv;
-        }
-        // rank-1 update with the pivot row read from lane lp, register row rp;
-        // then the owner of column k + 1 searches that column's pivot and
-        // publishes it for the next step.
-        const int k1 = k + 1;
-        const bool owner1 = k1 < n && wave == k1 % NWV;
-        const int c1 = owner1 ? k1 / NWV : -1;
-        // colv / pv, so that the pivot-row value read with readlane (a
-        // scalar) feeds the FMA directly; column k uses pv + 1, which turns
-        // column k into -D[i][k]/pv.  The pivot row is untouched (colv = 0).
-        double colv_s[RPL];
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) colv_s[r] = colv[r] * inv;
-        // columns in chunks: the pivot-row values come from register row rp
-        // (a scalar branch) of lane lp into scalar registers
-        constexpr int CHK = CPW % 7 == 0 ? 7 : (CPW % 4 == 0 ? 4 : 1);
-        static_for<0, CPW / CHK>([&](auto chc) __attribute__((always_inline)) {
-            constexpr int c0 = decltype(chc)::value * CHK;
-            double rv[CHK];
-            auto grab = [&](auto rr) __attribute__((always_inline)) {
-                constexpr int r = decltype(rr)::value;
-#pragma unroll
-                for (int j = 0; j < CHK; ++j) rv[j] = readlane_f64(M[r][c0 + j], lp);
-            };
-            if (rp == 0) grab(std::integral_constant<int, 0>{});
-            if constexpr (RPL > 1) { if (rp == 1) grab(std::integral_constant<int, 1>{}); }
-            if constexpr (RPL > 2) { if (rp == 2) grab(std::integral_constant<int, 2>{}); }
-            if constexpr (RPL > 3) { if (rp == 3) grab(std::integral_constant<int, 3>{}); }
-#pragma unroll
-            for (int j = 0; j < CHK; ++j) {
-                const int c = c0 + j;
-                const double r_ = (wave == vk && c == ck) ? pv + 1.0 : rv[j];
-#pragma unroll
-                for (int r = 0; r < RPL; ++r) M[r][c] = fma(-colv_s[r], r_, M[r][c]);
-            }
-        });
-        if (owner1) {
-            double col[RPL];
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) col[r] = 0.0;
-            static_for<0, CPW>([&](auto cc) __attribute__((always_inline)) {
-                constexpr int c = decltype(cc)::value;
-                if (c == c1) {
-#pragma unroll
-                    for (int r = 0; r < RPL; ++r) col[r] = M[r][c];
-                }
-            });
-            const uint32_t used1 = used | (lane == lp ? 1u << rp : 0u);
-            gj_search<RPL>(col, n, lane, used1, colbuf[b ^ 1], &piv_idx[b ^ 1], &piv_val[b ^ 1]);
-        }
-        if (lane == lp) used |= 1u << rp;
-    }
-    __syncthreads();
-
-    double* Dw = Dinv + (size_t)w * nn;
-    if (singular) {
-        // undefined inverse: NaN, log|det| = -inf, sign = 0
-        for (size_t q = tid; q < nn; q += NT) Dw[q] = __longlong_as_double(0x7ff8000000000000ll);
-        if (tid == 0) {
-            if (logdet) logdet[2 * w + spin] = s_flag == 1 ? -INFINITY : __longlong_as_double(0x7ff8000000000000ll);
-            if (sign) sign[2 * w + spin] = 0;
-            if (status) atomicOr(status + w, s_flag == 1 ? QSL_STATUS_SINGULAR : QSL_STATUS_NONFINITE);
-        }
-        return;
-    }
-    if (tid < 64) {
-        // log|det| = sum log|pivot|, sign = sign(permutation) prod sign(pivot)
-        double ld = 0.0;
-        int neg = 0;
-        for (int i = tid; i < n; i += 64) {
-            ld += log(fabs(rowpiv[i]));
-            neg += rowpiv[i] < 0.0;
-        }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            ld += __shfl_xor(ld, o);
-            neg += __shfl_xor(neg, o);
-        }
-        if (tid == 0) {
-            // parity of the pivot permutation by cycle counting (invp as scratch)
-            for (int i = 0; i < n; ++i) invp[i] = 0;
-            int cycles = 0;
-            for (int i = 0; i < n; ++i) {
-                if (invp[i]) continue;
-                ++cycles;
-                for (int j = i; !invp[j]; j = perm[j]) invp[j] = 1;
-            }
-            const int sg = ((neg + n - cycles) & 1) ? -1 : 1;
-            if (logdet) logdet[2 * w + spin] = ld;
-            if (sign) sign[2 * w + spin] = (int8_t)sg;
-            if (status && !isfinite(ld)) atomicOr(status + w, QSL_STATUS_NONFINITE);
-        }
-    }
-    __syncthreads();
-    for (int k = tid; k < n; k += NT) invp[perm[k]] = k;
-    __syncthreads();
-    // the pivot entries were left at pv during the elimination (the pivot row
-    // is never scaled); their value in the scaled representation is 1, and
-    // later updates of them only added terms: M[p_k][k] += 1 - pv_k
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const int i = lane + 64 * r;
-        if (i >= n) continue;
-        const int kp = invp[i];
-#pragma unroll
-        for (int c = 0; c < CPW; ++c)
-            if (wave + NWV * c == kp) M[r][c] += 1.0 - rowpiv[i];
-    }
-    // D^-1[invp[i]][perm[e]] = M[i][e] / pivot(i), staged QC rows at a time
-    int rowi[RPL];
-    double rs[RPL];
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const int i = lane + 64 * r;
-        rowi[r] = i < n ? invp[i] : -1;
-        rs[r] = i < n ? 1.0 / rowpiv[i] : 0.0;
-    }
-    for (int q0 = 0; q0 < n; q0 += QC) {
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            const int rr = rowi[r] - q0;
-            if (rr >= 0 && rr < QC) {
-#pragma unroll
-                for (int c = 0; c < CPW; ++c) {
-                    const int e = wave + NWV * c;
-                    if (e < n) stage[rr][perm[e]] = M[r][c] * rs[r];
-                }
-            }
-        }
-        __syncthreads();
-        const int rows = min(QC, n - q0);
-        for (int q = tid; q < rows * n; q += NT) {
-            const int rr = q / n, cc = q % n;
-            Dw[(size_t)(q0 + rr) * n + cc] = stage[rr][cc];
-        }
-        __syncthreads();
-    }
-}
+// Shapes: n <= 16 NT.
+template <int NT>
+struct GJT {
+    static constexpr int CT = 2;                    // D column tiles per updating wave
+    static constexpr int NU = (NT + CT - 1) / CT;   // updating waves
+    static constexpr int THREADS = (NU + 1) * 64;   // and the panel wave
+    static constexpr int WPE = NT <= 4 ? 4 : NT <= 9 ? 3 : 2;  // waves per SIMD
+    static constexpr int NP = 16 * NT;
+    static constexpr int RPL = (NP + 63) / 64;      // panel rows per lane
+    static constexpr bool EXACT = NT <= 8;          // pivot by the full |a| (else to 2^-12)
+    // row strides in doubles: 8 mod 16, so that four rows of 16 consecutive
+    // values cover every LDS bank evenly (and 8 spare entries)
+    static constexpr int LS = NP + 8;
+    static constexpr int PS = 16 * CT + 8;
+    // doubles: the panel handed over, F of two panels, pivot rows per wave
+    static constexpr int MAIN = 3 * 16 * LS + NU * 16 * PS;
+    // output staging (over all that): QC rows of D^-1
+    static constexpr int SS = NP + 2;
+    static constexpr int QC = MAIN / SS < NP ? MAIN / SS : NP;
+};
 
 // Flag accesses in LDS.  The LDS executes the DS instructions of one wave in
-// program order, so a flag written after a wave's data writes is seen only
+// program order, so a flag written after a wave's data accesses is seen only
 // once they are done, and data read after a flag was seen is the data
 // published before it; only the compiler has to keep the order (the
 // signal fences), no wait is needed.
 __device__ __forceinline__ int flag_load(int* f) {
     const int v = __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    return v;
+    return __builtin_amdgcn_readfirstlane(v);
 }
 __device__ __forceinline__ void flag_store(int* f, int v) {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __hip_atomic_store(f, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-
-// ------------------------------------------------------- 128 < n <= 224
-// Half-wave layout (eight waves): lane li (< 32) of either half of a wave
-// owns the D rows i = li + 32 r (r < RPL) and holds M[r][c] for CPW columns;
-// 7 x 14 values per lane cover 224 x 224 with little padding.  The two
-// halves of a wave own a pair of consecutive columns (column e: wave
-// (e / 2) % 8, half e % 2, register column e / 16 before rotations), and a
-// round publishes two elimination steps through LDS.  The wave owning the
-// next round's columns looks ahead: it applies the current round's two
-// steps to its register column 0 (both halves, in place), finds the first
-// column's pivot, publishes its multipliers -D[i][k]/pv (0 in the pivot
-// row), reads them back in the second half, applies that step to the
-// second column and finds its pivot.  The other waves wait once per round
-// and apply the two rank-1 updates in order: every half writes its segment
-// of the pivot row (lane p % 32, register row p / 32) to LDS and reads it
-// back broadcast; the owner of column k substitutes pv + 1 in its slot,
-// which turns the column into -D[i][k]/pv (the pivot row itself is left
-// unscaled).  Steps a look-ahead applied in place are skipped: a zero
-// pivot-row entry in the owner's second half, and the look-ahead wave
-// leaves out its register column 0 for the round it looked ahead from.
-// No barrier per round: the publisher raises a flag in LDS, each wave
-// records the last round whose inputs it has read, and a publisher
-// overwrites a buffer (four, by round mod 4) only once every wave has read
-// it.  A wave's register columns rotate by one after the round of its own
-// columns, so the pair a wave handles next is always its register column
-// 0; after R rotations register column c holds the D columns
-// e = 16 ((c + R) mod CPW) + 2 v + h.
-
-// v[r] for a wave-uniform r < RPL <= 8, by a three-level tree of selects
-// on scalar conditions, not a chain of RPL - 1
-template <int RPL>
-__device__ __forceinline__ double select_row(const double (&v)[RPL], int r) {
-    static_assert(RPL <= 8, "three levels");
-    double t[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) t[q] = v[q < RPL ? q : RPL - 1];
-#pragma unroll
-    for (int s = 0; s < 3; ++s)
-#pragma unroll
-        for (int q = 0; q < (4 >> s); ++q) t[q] = ((r >> s) & 1) ? t[2 * q + 1] : t[2 * q];
-    return t[0];
+// Waits until *f >= v; false when the bound on the wait was reached.
+__device__ __forceinline__ bool flag_wait(int* f, int v) {
+    for (int it = 0; it < (1 << 22); ++it)
+        if (flag_load(f) >= v) return true;
+    return false;
 }
 
-// Pivot of the half `half` of a register column: its row si (0x7fffffff if
-// none), value pv and reciprocal inv, all wave-uniform.  One 32-bit key per
-// candidate row (unused, not past n, not NaN): the high word of |a| (sign
-// 0, exponent, 20 significand bits) with its low 8 bits replaced by
-// 255 - i; 0 elsewhere.  As unsigned integers the keys order like |a| to
-// 2^-12 relative, and among values that close the smallest row wins; the
-// row comes back from the key.  The maximum runs inside rows of 16 lanes by
-// DPP (quad swaps, half-row and row mirrors), then over the half's two
-// rows.  1/pv: hardware reciprocal and two Newton steps (the error squares
-// each step).
-template <int RPL>
-__device__ __forceinline__ void gjh2_pivot(const double (&col)[RPL], int li, int half, uint32_t used, int& si,
-                                           double& pv, double& inv) {
-    uint32_t best = 0;
+template <int NT>
+struct GJShared {
+    double main[GJT<NT>::MAIN];
+    double pvs[GJT<NT>::NP];   // pivot of step k
+    double row[16];            // the panel wave's pivot row
+    int perm[GJT<NT>::NP];     // row of step k
+    uint32_t ord[16][4];       // byte i / 16 of row i % 16: 1 + the step that took row i (0: none)
+    int xready;                // last panel handed over to the panel wave
+    int xfree;                 // last panel whose columns were taken from there
+    int bad;                   // 1: zero pivot, 2: non-finite pivot
+    // (the panel first: its addresses are constants within an LDS
+    // instruction's offset)
+    __device__ double* X() { return main; }
+    __device__ double* F(int p) { return main + (1 + (p & 1)) * 16 * GJT<NT>::LS; }
+    __device__ uint8_t& ord_of(int i) { return ((uint8_t*)ord)[(i & 15) * 16 + (i >> 4)]; }
+};
+
+// One stage of the wave maximum of a 32-bit key: quad swaps, half-row and
+// row mirrors inside rows of 16 lanes, then the row results passed on to the
+// next row and the upper half; lane 63 ends with the maximum.
+template <int STAGE>
+__device__ __forceinline__ uint32_t umax_stage(uint32_t x) {
+    constexpr int ctrl[6] = {0xB1, 0x4E, 0x141, 0x140, 0x142, 0x143};
+    return max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl[STAGE], STAGE == 4 ? 0xa : STAGE == 5 ? 0xc : 0xf,
+                                                        0xf, false));
+}
+
+// What one inversion reads of its Job.
+struct GJArgs {
+    const void* C;
+    double* Dinv;
+    double* logdet;
+    int8_t* sign;
+    uint32_t* status;
+    int n, spin, mode;
+};
+__host__ __device__ __forceinline__ GJArgs gj_args(const Job& j) {
+    return GJArgs{j.C, j.Dinv, j.logdet, j.sign, j.status, j.n, j.spin, j.mode};
+}
+
+// Search keys of an entry x of row i.  EXACT: the high word of |x| above a
+// set bit (rows alike in it are told apart by their low words afterwards);
+// else exponent and 20 significand bits above 255 - i, which gives the row
+// back and the smallest of rows alike.
+template <bool EXACT>
+__device__ __forceinline__ uint32_t gj_key(double x, int i) {
+    const uint32_t hi = (uint32_t)((uint64_t)__double_as_longlong(x) >> 32);
+    return EXACT ? hi << 1 | 1u : (hi & 0x7fffff00u) | (uint32_t)(255 - i);
+}
+// Whether the largest key is no normal finite number's.
+template <bool EXACT>
+__device__ __forceinline__ bool gj_odd(uint32_t key) {
+    return EXACT ? key - 0x00200000u >= 0xffc00000u : key - 0x00100000u >= 0x7fe00000u;
+}
+template <bool EXACT>
+__device__ __forceinline__ double gj_recip(double pv) {
+    if constexpr (EXACT) return 1.0 / pv;
+    // hardware reciprocal and two Newton steps
+    double inv = __builtin_amdgcn_rcp(pv);
+    inv = fma(inv, fma(-pv, inv, 1.0), inv);
+    return fma(inv, fma(-pv, inv, 1.0), inv);
+}
+
+// A panel one of whose largest keys was no ordinary number's: its steps on
+// the panel in LDS, with NaN left out of the search.  Returns 0, or 1 where no
+// row or a zero is left, 2 where the pivot is infinite.
+template <int NT>
+__device__ __forceinline__ int gjt_panel_careful(GJShared<NT>& S, int p, int n16, int lane) {
+    using P = GJT<NT>;
+    constexpr int LS = P::LS;
+    double *X = S.X(), *F = S.F(p);
+#pragma unroll 1
+    for (int k = 0; k < 16; ++k) {
+        uint64_t best = 0;  // |x| and 255 - i, or the key, to be largest
+        int at = 0;
+#pragma unroll 1
+        for (int row = lane; row < n16; row += 64) {
+            const double x = X[k * LS + row];
+            if (S.ord_of(row) != 0 || x != x) continue;
+            const uint64_t b = P::EXACT ? ((uint64_t)__double_as_longlong(x) << 1 | 1u) : gj_key<false>(x, row);
+            if (b > best) { best = b; at = row; }
+        }
+#pragma unroll 1
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint64_t ob = (uint64_t)__shfl_xor((unsigned long long)best, o);
+            const int oa = __shfl_xor(at, o);
+            if (ob > best || (ob == best && oa < at)) { best = ob; at = oa; }
+        }
+        if (best == 0) return 1;
+        const double pv = X[k * LS + at];
+        if (pv == 0.0) return 1;
+        if (!isfinite(pv)) return 2;
+        const double inv = gj_recip<P::EXACT>(pv);
+        if (lane == 0) {
+            S.pvs[16 * p + k] = pv;
+            S.perm[16 * p + k] = at;
+            S.ord_of(at) = (uint8_t)(16 * p + k + 1);
+        }
+#pragma unroll 1
+        for (int row = lane; row < P::NP; row += 64) {
+            const double x = X[k * LS + row];
+            const double f = row == at ? 0.0 : -(x * inv);
+            F[k * LS + row] = f;
+#pragma unroll 1
+            for (int c = k + 1; c < 16; ++c)
+                if (row != at) X[c * LS + row] = fma(f, X[c * LS + at], X[c * LS + row]);
+            X[k * LS + row] = fma(f, pv + 1.0, x);
+        }
+    }
+    return 0;
+}
+
+// The panel wave.  Lane l holds rows l + 64 r of the panel's 16 columns.  One
+// wave issues an instruction in about five cycles, a branch costs 25 and an
+// LDS write 16 per eight bytes of a lane, so a step costs what it issues:
+// each lane takes the reciprocal of its own candidate during the maximum, the
+// next column is updated and searched first (its pivot-row entry comes by
+// lane exchange), the pivot row reaches the columns after it through LDS, and
+// the stages of the maximum stand between their updates.  A largest key
+// that is no ordinary number's is only noted; the panel is then done again.
+template <int NT>
+__device__ __forceinline__ void gjt_panels(const GJArgs& j, GJShared<NT>& S, int w, int lane) {
+    using P = GJT<NT>;
+    constexpr int RPL = P::RPL, LS = P::LS;
+    constexpr bool EXACT = P::EXACT;
+    const int n = j.n, np = (n + 15) >> 4;
+    uint64_t open[RPL];  // rows not yet used
+    int mine[RPL];       // this lane's rows (those past NP: the spare entries)
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
-        const int i = li + 32 * r;
-        const uint32_t hi = (uint32_t)((uint64_t)__double_as_longlong(col[r]) >> 32) & 0x7fffffffu;
-        const uint32_t keep = ((used >> r) & 1u) - 1u;  // all ones for a candidate row
-        const uint32_t kr = ((hi & ~0xFFu) | (uint32_t)(255 - i)) & keep;
-        best = max(best, col[r] == col[r] ? kr : 0u);
+        const int row = lane + 64 * r;
+        open[r] = __ballot(row < 16 * np);
+        mine[r] = row < P::NP ? row : P::NP + (lane & 7);
     }
-    best = max(best, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)best, 0xB1, 0xf, 0xf, false));
-    best = max(best, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)best, 0x4E, 0xf, 0xf, false));
-    best = max(best, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)best, 0x141, 0xf, 0xf, false));
-    best = max(best, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)best, 0x140, 0xf, 0xf, false));
-    const int l0 = 32 * half;
-    const uint32_t gk = max((uint32_t)__builtin_amdgcn_readlane((int)best, l0),
-                            (uint32_t)__builtin_amdgcn_readlane((int)best, l0 + 16));
-    const bool any = gk != 0;
-    si = any ? 255 - (int)(gk & 0xFF) : 0x7fffffff;
-    const int rs = any ? si >> 5 : 0, ls = any ? si & 31 : 0;
-    double cv = col[0];
+    int inversions = 0;  // of the pivot permutation, by lanes
+    __builtin_amdgcn_s_setprio(3);
+#pragma unroll 1
+    for (int p = 0; p < np; ++p) {
+        uint64_t before[RPL];  // the open rows as the panel begins
 #pragma unroll
-    for (int r = 1; r < RPL; ++r) cv = rs == r ? col[r] : cv;
-    pv = any ? readlane_f64(cv, l0 + ls) : 0.0;
-    inv = __builtin_amdgcn_rcp(pv);
-    inv = fma(inv, fma(-pv, inv, 1.0), inv);
-    inv = fma(inv, fma(-pv, inv, 1.0), inv);
-}
-
-template <int RPL, int CPW, typename Tin>
-__device__ __forceinline__ void gjh2_body(const Job& j, int bx) {
-    const Tin* __restrict__ C = (const Tin*)j.C;
-    const int n = j.n, spin = j.spin;
-    double* __restrict__ Dinv = j.Dinv;
-    double* __restrict__ logdet = j.logdet;
-    int8_t* __restrict__ sign = j.sign;
-    uint32_t* __restrict__ status = j.status;
-    constexpr int NG = 16, NT = 512;
-    constexpr int NR = 32 * RPL;  // capacity in D rows (MO index i)
-    constexpr int NC = NG * CPW;  // capacity in D columns (electron index e)
-    constexpr int QC = 32;        // rows of D^-1 staged per output pass
-    constexpr int NB = 4;         // publication buffers, by round mod NB
-    __shared__ double colbuf[NB][2][NR];
-    __shared__ int piv_idx[NB][2];
-    __shared__ double piv_val[NB][2];
-    __shared__ __align__(16) double prow[NG][CPW];
-    __shared__ int perm[NC];
-    __shared__ int invp[NR];
-    __shared__ double rowpiv[NR];
-    __shared__ double stage[QC][NC > NR ? NC : NR];
-    __shared__ double red_ld[NT / 64];
-    __shared__ int red_neg[NT / 64];
-    __shared__ int s_flag;
-    __shared__ int pub;           // last round whose pivots and columns are published
-    __shared__ int prog[NT / 64]; // last round each wave has read its inputs of
-    __shared__ int s_abort;       // a wait ran over its bound
-
-    const int w = bx;
-    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, h = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
-    const int g = wave + 8 * h;                                  // pivot-row segment of this half
-    const size_t nn = (size_t)n * n;
-    const Tin* C1 = C + (size_t)w * 5 * nn;  // derivative 0 block
-    const int nr = (n + 1) / 2;              // rounds
-
-    double M[RPL][CPW];
+        for (int r = 0; r < RPL; ++r) before[r] = open[r];
+        int code = flag_wait(&S.xready, p) ? 0 : 2;
+        double *Xb = S.X(), *Fb = S.F(p);
+        double X[RPL][16];
 #pragma unroll
-    for (int c = 0; c < CPW; ++c)
+        for (int r = 0; r < RPL; ++r)
 #pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            const int e = 16 * c + 2 * wave + h, i = li + 32 * r;
-            const Tin v = gmem(C1)[min(e, n - 1) * n + min(i, n - 1)];
-            M[r][c] = (e < n && i < n) ? (double)v : 0.0;
-        }
-    for (int k = tid; k < NB * 2 * NR; k += NT) colbuf[k / (2 * NR)][(k / NR) & 1][k % NR] = 0.0;
-    if (tid == 0) { s_flag = 0; pub = -1; s_abort = 0; }
-    if (tid < NT / 64) prog[tid] = -1;
-    __syncthreads();
-    constexpr int SPIN_LIMIT = 1 << 22;
-    auto give_up = [&]() {
-        if (lane == 0) flag_store(&s_abort, 1);
-        return false;
-    };
-    auto stop = [&](int it) {  // the abort flag is polled every 64th time
-        return (it & 63) == 63 && (it >= SPIN_LIMIT || __builtin_amdgcn_readfirstlane(flag_load(&s_abort)));
-    };
-    auto wait_consumed = [&](int round) -> bool {  // every wave has read the inputs of round
-        for (int it = 0;; ++it) {
-            const int pg = lane < NT / 64 ? flag_load(&prog[lane]) : 0x7fffffff;
-            if (__ballot(pg < round) == 0) return true;
-            if (stop(it)) return give_up();
-            if (it >= 4) __builtin_amdgcn_s_sleep(1);
-        }
-    };
-    auto row_bit = [&](int p) -> uint32_t { return li == (p & 31) ? 1u << (p >> 5) : 0u; };
-    uint32_t used = 0;  // bit r: row li + 32 r already a pivot row, or past n
-#pragma unroll
-    for (int r = 0; r < RPL; ++r)
-        if (li + 32 * r >= n) used |= 1u << r;
-    int rot = 0;  // rotations of this wave's register columns (mod CPW)
-
-    // Look-ahead of round rr by its owner wave: register column 0 holds the
-    // columns 2 rr (half 0) and 2 rr + 1 (half 1) with every earlier step
-    // applied; `u` marks the earlier pivot rows.  Returns false if a wait ran
-    // over its bound.
-    auto look_ahead = [&](int rr, uint32_t u) -> bool {
-        const int b = rr % NB;
-        const int pg = lane < NT / 64 ? flag_load(&prog[lane]) : 0x7fffffff;
-        double col[RPL];
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) col[r] = M[r][0];
-        int sc;
-        double pc, ic;
-        gjh2_pivot<RPL>(col, li, 0, u, sc, pc, ic);
-        bool ok = true;
-        if (rr >= NB && __ballot(pg < rr - NB) != 0) ok = wait_consumed(rr - NB);
-        if (h == 0) {
+            for (int c = 0; c < 16; ++c) X[r][c] = Xb[c * LS + mine[r]];
+        uint32_t kr[RPL], key = 0;   // the searched column's keys, their largest
+        double cand = 0, linv = 0;   // this lane's best candidate, its reciprocal
+        auto keys = [&](auto kc) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value;
 #pragma unroll
             for (int r = 0; r < RPL; ++r) {
-                const int i = li + 32 * r;
-                if (i < n) colbuf[b][0][i] = i == sc ? 0.0 : -col[r] * ic;
+                const uint32_t q = gj_key<EXACT>(X[r][k], lane + 64 * r);
+                kr[r] = __builtin_amdgcn_inverse_ballot_w64(open[r]) ? q : 0u;
+                const bool up = r == 0 || kr[r] > key;
+                cand = up ? X[r][k] : cand;
+                key = up ? kr[r] : key;
             }
-        }
-        if (lane == 0) { piv_idx[b][0] = sc; piv_val[b][0] = pc; }
-        if (2 * rr + 1 < n) {
-            // the first step on the second column (half 1), in place: its
-            // multipliers back from the buffer, the pivot row's entry of
-            // the second column from lane 32 + sc % 32
-            double cv[RPL];
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) cv[r] = colbuf[b][0][li + 32 * r];
-            const double xc = sc < n ? readlane_f64(select_row<RPL>(col, sc >> 5), 32 + (sc & 31)) : 0.0;
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                const double y = fma(cv[r], xc, M[r][0]);
-                M[r][0] = h ? y : M[r][0];
-                col[r] = M[r][0];
-            }
-            int sd;
-            double pd, id;
-            gjh2_pivot<RPL>(col, li, 1, u | (sc < n ? row_bit(sc) : 0u), sd, pd, id);
-            if (h == 1) {
+        };
+        bool odd = false;
+        keys(std::integral_constant<int, 0>{});
+        linv = gj_recip<EXACT>(cand);
+        static_for<0, 6>([&](auto sc) __attribute__((always_inline)) { key = umax_stage<decltype(sc)::value>(key); });
+        static_for<0, 16>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value;
+            const uint32_t sk = (uint32_t)__builtin_amdgcn_readlane((int)key, 63);
+            odd |= gj_odd<EXACT>(sk);
+            uint64_t m[RPL];  // the pivot's lane
+            int rs = 0, ls;
+            double inv, pv;
+            if constexpr (EXACT) {
+                int cnt = 0;
 #pragma unroll
                 for (int r = 0; r < RPL; ++r) {
-                    const int i = li + 32 * r;
-                    if (i < n) colbuf[b][1][i] = i == sd ? 0.0 : -col[r] * id;
+                    m[r] = __ballot(kr[r] == sk);
+                    cnt += __popcll(m[r]);
                 }
-            }
-            if (lane == 0) { piv_idx[b][1] = sd; piv_val[b][1] = pd; }
-        }
-        if (ok && lane == 0) flag_store(&pub, rr);
-        return ok;
-    };
-    if (wave == 0 && !look_ahead(0, used)) {
-        // a wait ran over its bound: reported below
-    }
-
-    bool singular = false;
-    auto bad_pivot = [&](int p, double pv) {
-        if (p >= n || !(pv != 0.0) || !isfinite(pv)) {
-            singular = true;
-            if (tid == 0) s_flag = isfinite(pv) || p >= n ? 1 : 2;
-            return true;
-        }
-        return false;
-    };
-    for (int rd = 0; rd < nr; ++rd) {
-        const int b = rd % NB;
-        const int ns = 2 * rd + 1 < n ? 2 : 1;  // steps in this round
-        bool live = true;
-        int seen = rd;
-        for (int it = 0;; ++it) {
-            seen = __builtin_amdgcn_readfirstlane(flag_load(&pub));
-            if (seen >= rd) break;
-            if (stop(it)) { live = give_up(); break; }
-            if (it >= 4) __builtin_amdgcn_s_sleep(1);
-        }
-        if (!live) break;
-        // a wave behind the published rounds takes issue priority over its
-        // SIMD mates until it has caught up
-        if (seen >= rd + 2) __builtin_amdgcn_s_setprio(2);
-        else if (seen == rd + 1) __builtin_amdgcn_s_setprio(1);
-        else __builtin_amdgcn_s_setprio(0);
-        const int pa = __builtin_amdgcn_readfirstlane(piv_idx[b][0]);
-        const double pva = readlane_f64(piv_val[b][0], 0);
-        const int pb = ns == 2 ? __builtin_amdgcn_readfirstlane(piv_idx[b][1]) : 0;
-        const double pvb = ns == 2 ? readlane_f64(piv_val[b][1], 0) : 1.0;
-        double colv[RPL];  // multipliers of the round's first step
+                if (__builtin_expect(cnt != 1, 0)) {
+                    // alike in the high word: the largest low word, then the
+                    // smallest row
+                    uint32_t lo = 0;
 #pragma unroll
-        for (int r = 0; r < RPL; ++r) colv[r] = colbuf[b][0][li + 32 * r];
-        if (bad_pivot(pa, pva) || (ns == 2 && bad_pivot(pb, pvb))) break;
-        const int own = rd & 7;  // the wave owning this round's columns
-        const int r1 = rd + 1;
-        const bool la = r1 < nr && wave == (r1 & 7);  // this wave looks ahead
-        if (la) {
-            // the round's steps on register column 0 (both halves, in place;
-            // the regular update below leaves column 0 out), then round
-            // rd + 1's pivots.  It is the step's critical path: first thing
-            // after the inputs, at raised priority over the SIMD mate.
-            __builtin_amdgcn_s_setprio(3);
-            double m0[RPL];
+                    for (int r = 0; r < RPL; ++r)
+                        if (kr[r] == sk) lo = max(lo, (uint32_t)__double_as_longlong(X[r][k]));
+                    static_for<0, 6>([&](auto sc) __attribute__((always_inline)) { lo = umax_stage<decltype(sc)::value>(lo); });
+                    lo = (uint32_t)__builtin_amdgcn_readlane((int)lo, 63);
+                    bool found = false;
 #pragma unroll
-            for (int r = 0; r < RPL; ++r) m0[r] = M[r][0];
-            {
-                const double xs = select_row<RPL>(m0, pa >> 5);
-                const double x0 = readlane_f64(xs, pa & 31), x1 = readlane_f64(xs, 32 + (pa & 31));
-                const double xm = h ? x1 : x0;
-#pragma unroll
-                for (int r = 0; r < RPL; ++r) M[r][0] = fma(colv[r], xm, M[r][0]);
-            }
-            if (ns == 2) {
-                double cb[RPL];
-#pragma unroll
-                for (int r = 0; r < RPL; ++r) { cb[r] = colbuf[b][1][li + 32 * r]; m0[r] = M[r][0]; }
-                const double xs = select_row<RPL>(m0, pb >> 5);
-                const double x0 = readlane_f64(xs, pb & 31), x1 = readlane_f64(xs, 32 + (pb & 31));
-                const double xm = h ? x1 : x0;
-#pragma unroll
-                for (int r = 0; r < RPL; ++r) M[r][0] = fma(cb[r], xm, M[r][0]);
-            }
-            const bool ok = look_ahead(r1, used | row_bit(pa) | (ns == 2 ? row_bit(pb) : 0u));
-            __builtin_amdgcn_s_setprio(0);
-            if (!ok) break;
-        }
-        // the round's steps in order; column 2 rd takes pv + 1 (its owner's
-        // half 0), which turns it into -D[i][k]/pv; its owner's half 1 holds
-        // column 2 rd + 1, which the look-ahead has already updated for the
-        // first step (entry 0)
-#pragma unroll 1
-        for (int sidx = 0; sidx < ns; ++sidx) {
-            const int p = sidx ? pb : pa;
-            const double pv = sidx ? pvb : pva;
-            if (sidx) {
-#pragma unroll
-                for (int r = 0; r < RPL; ++r) colv[r] = colbuf[b][1][li + 32 * r];
-            }
-            if (sidx + 1 == ns && lane == 0) flag_store(&prog[wave], rd);  // after the reads of the round's inputs
-            const int lp = p & 31, rp = p >> 5;
-            if (li == lp) {
-                static_for<0, RPL>([&](auto rr) __attribute__((always_inline)) {
-                    constexpr int r = decltype(rr)::value;
-                    if (rp == r) {
-#pragma unroll
-                        for (int c = 0; c < CPW; ++c) prow[g][c] = M[r][c];
-                        asm volatile("; pivot row %0" ::"n"(r));
+                    for (int r = 0; r < RPL; ++r) {
+                        const uint64_t b = __ballot(kr[r] == sk && (uint32_t)__double_as_longlong(X[r][k]) == lo);
+                        m[r] = found ? 0 : b & (0 - b);
+                        found |= b != 0;
                     }
-                });
+                    double y = X[0][k];
+#pragma unroll
+                    for (int r = 1; r < RPL; ++r) y = m[r] ? X[r][k] : y;
+                    cand = y;
+                    linv = 1.0 / y;
+                }
+#pragma unroll
+                for (int r = 1; r < RPL; ++r) rs = m[r] ? r : rs;
+                uint64_t mm = m[0];
+#pragma unroll
+                for (int r = 1; r < RPL; ++r) mm |= m[r];
+                ls = __builtin_ctzll(mm | 1ull << 63);
+            } else {
+                const int si = (int)(~sk & 0xffu);
+                rs = si >> 6;
+                ls = si & 63;
+#pragma unroll
+                for (int r = 0; r < RPL; ++r) m[r] = rs == r ? 1ull << ls : 0;
             }
-            if (wave == own && lane == 0) {
-                if (sidx == 0) {
-                    prow[own][0] = pv + 1.0;
-                    prow[own + 8][0] = 0.0;
+            inv = readlane_f64(linv, ls);
+            pv = readlane_f64(cand, ls);
+            double x1 = 0.0;  // the pivot row's entry of the next column
+            if constexpr (k + 1 < 16) {
+                double y[RPL];
+#pragma unroll
+                for (int r = 0; r < RPL; ++r) {
+                    y[r] = X[r][k + 1];
+                    asm("" : "+v"(y[r]));  // (values, not addresses, are selected)
+                }
+#pragma unroll
+                for (int r = 1; r < RPL; ++r) y[0] = rs == r ? y[r] : y[0];
+                x1 = readlane_f64(y[0], ls);
+            }
+            // the pivot row of the columns after the next one, by way of LDS
+            constexpr int c0 = (k + 2) & ~1;
+            auto put = [&](auto rc) __attribute__((always_inline)) {
+                constexpr int r = decltype(rc)::value;
+                if (__builtin_amdgcn_inverse_ballot_w64(m[r])) {
+#pragma unroll
+                    for (int c = c0; c < 16; c += 2) *(f64x2*)&S.row[c] = f64x2{X[r][c], X[r][c + 1]};
+                    S.pvs[16 * p + k] = pv;
+                    S.perm[16 * p + k] = lane + 64 * r;
+                }
+                if constexpr (RPL > 1) asm volatile("; pivot row %0" ::"n"(r));
+            };
+            using R0 = std::integral_constant<int, 0>;
+            using R1 = std::integral_constant<int, (RPL > 1 ? 1 : 0)>;
+            using R2 = std::integral_constant<int, (RPL > 2 ? 2 : 0)>;
+            using R3 = std::integral_constant<int, (RPL > 3 ? 3 : 0)>;
+            if constexpr (RPL == 1) put(R0{});
+            else if constexpr (RPL == 2) {
+                if (rs == 0) put(R0{});
+                else put(R1{});
+            } else {
+                if (rs < 2) {
+                    if (rs == 0) put(R0{});
+                    else put(R1{});
                 } else {
-                    prow[own + 8][0] = pv + 1.0;
+                    if (RPL == 3 || rs == 2) put(R2{});
+                    else put(R3{});
                 }
             }
-            double pr[CPW];
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            double rv[16], f[RPL];
 #pragma unroll
-            for (int c = 0; c < CPW; ++c) pr[c] = prow[g][c];
-            if (!la) {
+            for (int c = k + 2; c < 16; ++c) rv[c] = S.row[c];
+            const double pv1 = pv + 1.0;
 #pragma unroll
-                for (int r = 0; r < RPL; ++r) M[r][0] = fma(colv[r], pr[0], M[r][0]);
+            for (int r = 0; r < RPL; ++r) {
+                const double fr = -(X[r][k] * inv);
+                f[r] = __builtin_amdgcn_inverse_ballot_w64(m[r]) ? 0.0 : fr;
+                open[r] &= ~m[r];
+                X[r][k] = fma(f[r], pv1, X[r][k]);
+                if constexpr (k + 1 < 16) X[r][k + 1] = fma(f[r], x1, X[r][k + 1]);
             }
+            auto col = [&](auto cc) __attribute__((always_inline)) {
+                constexpr int c = decltype(cc)::value;
+                if constexpr (c < 16) {
 #pragma unroll
-            for (int c = 1; c < CPW; ++c)
+                    for (int r = 0; r < RPL; ++r) X[r][c] = fma(f[r], rv[c], X[r][c]);
+                }
+            };
+            auto put_f = [&](int r) __attribute__((always_inline)) {
+                Fb[k * LS + mine[r]] = f[r];
+            };
+            if constexpr (k + 1 < 16) {
+                keys(std::integral_constant<int, k + 1>{});
+                linv = gj_recip<EXACT>(cand);
+                static_for<0, 6>([&](auto sc) __attribute__((always_inline)) {
+                    constexpr int st = decltype(sc)::value;
+                    key = umax_stage<st>(key);
+                    if constexpr (st < RPL) put_f(st);
+                    if constexpr (st >= 2) {  // (the pivot row is back from LDS)
+                        col(std::integral_constant<int, k + 2 * st - 2>{});
+                        col(std::integral_constant<int, k + 2 * st - 1>{});
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                static_for<k + 10, (k + 10 < 16 ? 16 : k + 10)>(col);
+            } else {
 #pragma unroll
-                for (int r = 0; r < RPL; ++r) M[r][c] = fma(colv[r], pr[c], M[r][c]);
-            used |= row_bit(p);
-            if (tid == 0) {
-                perm[2 * rd + sidx] = p;
-                rowpiv[p] = pv;
+                for (int r = 0; r < RPL; ++r) put_f(r);
             }
+        });
+        if (__builtin_expect(odd || code, 0)) {
+            if (!code) code = gjt_panel_careful<NT>(S, p, 16 * np, lane);
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+                const int row = lane + 64 * r;
+                open[r] = __ballot(row < 16 * np && S.ord_of(row & 255) == 0);
+            }
+            if (code && lane == 0) S.bad = code;
+        } else {
+            // the panel's columns, for the wave that owns them
+#pragma unroll
+            for (int r = 0; r < RPL; ++r)
+#pragma unroll
+                for (int c = 0; c < 16; ++c) Xb[c * LS + mine[r]] = X[r][c];
+            if (lane < 16) S.ord_of(S.perm[16 * p + lane]) = (uint8_t)(16 * p + lane + 1);
         }
-        if (wave == own) {  // both halves done with register column 0
-            double t0[RPL];
+        __syncthreads();
+        if (code) return;
+        // the inversions that this panel's rows add to the permutation, lane
+        // k < 16 those of step k (the smaller rows still open when it was
+        // taken)
+        {
+            const int row = S.perm[16 * p + (lane & 15)];
+            int below = 0;
 #pragma unroll
-            for (int r = 0; r < RPL; ++r) t0[r] = M[r][0];
+            for (int r = 0; r < RPL; ++r) {
+                const int d = row - 64 * r;
+                below += __popcll(before[r] & (d >= 64 ? ~0ull : d > 0 ? (1ull << d) - 1 : 0ull));
+            }
 #pragma unroll
-            for (int c = 0; c + 1 < CPW; ++c)
-#pragma unroll
-                for (int r = 0; r < RPL; ++r) M[r][c] = M[r][c + 1];
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) M[r][CPW - 1] = t0[r];
-            rot = rot + 1 == CPW ? 0 : rot + 1;
+            for (int k = 0; k < 16; ++k) below -= k < lane && __builtin_amdgcn_readlane(row, k) < row;
+            inversions += lane < 16 ? below : 0;
         }
     }
+    __builtin_amdgcn_s_setprio(0);
+    // log|det| = sum log|pivot|, by rows: those of a lane, then the lanes (up
+    // to 128 rows), or lanes 0 .. 63 of each 64 rows, then those in order
+    double ld = 0.0, part = 0.0;
+    int neg = inversions;
+#pragma unroll 1
+    for (int r = 0; r < RPL; ++r) {
+        const int row = lane + 64 * r;
+        double lg = 0.0;
+        if (row < n) {
+            const double v = S.pvs[(int)S.ord_of(row) - 1];
+            lg = log(fabs(v));
+            neg += v < 0.0;
+        }
+        part += lg;
+        if (EXACT && r + 1 < RPL) continue;
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o);
+        ld += part;
+        part = 0.0;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) neg += __shfl_xor(neg, o);
+    if (lane == 0) {
+        if (j.logdet) j.logdet[2 * (size_t)w + j.spin] = ld;
+        if (j.sign) j.sign[2 * (size_t)w + j.spin] = (neg & 1) ? -1 : 1;
+        if (j.status && !isfinite(ld)) atomicOr(j.status + w, QSL_STATUS_NONFINITE);
+    }
+}
+
+// Register tiles of an updating wave from C_1[e][i], the identity past n (so
+// that the last panel has 16 columns; its inverse and determinant add
+// nothing).  A whole column tile's loads are in flight at once.  A row is
+// read past its end (into the next row, or the gradient block after C_1)
+// rather than clamped, except where the matrix is too small for that.
+template <int NT, typename Tin>
+__device__ __forceinline__ void gjt_load(const Tin* __restrict__ C1, int n, int u, int lane,
+                                         f64x4 (&acc)[NT][GJT<NT>::CT]) {
+    using P = GJT<NT>;
+    const int li = lane & 15, lg = lane >> 4;
+#pragma unroll
+    for (int ct = 0; ct < P::CT; ++ct) {
+        Tin v[4][NT];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int e = 16 * (u + P::NU * ct) + lg + 4 * r;
+            const Tin* row = C1 + min(e, n - 1) * n;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) v[r][t] = gmem(row)[NT <= 2 ? min(16 * t + li, n - 1) : 16 * t + li];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int e = 16 * (u + P::NU * ct) + lg + 4 * r;
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                acc[t][ct][r] = e < n && 16 * t + li < n ? (double)v[r][t] : (e == 16 * t + li ? 1.0 : 0.0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Staged rows q0 .. of D^-1 to memory, between the workgroup's barriers.
+template <int NT>
+__device__ __forceinline__ void gjt_copy_out(const GJArgs& j, GJShared<NT>& S, int w, int q0, int wave, int lane) {
+    using P = GJT<NT>;
+    const int n = j.n, rows = min(P::QC, n - q0);
+    double* Dw = j.Dinv + (size_t)w * n * n + (size_t)q0 * n;
     __syncthreads();
-    if (s_abort) {  // reported as a non-finite result
-        singular = true;
-        if (tid == 0) s_flag = 2;
+    for (int rr = wave; rr < rows; rr += P::NU + 1)
+        for (int cc = lane; cc < n; cc += 64) gmem(Dw)[rr * n + cc] = S.main[rr * P::SS + cc];
+    __syncthreads();
+}
+
+// An updating wave: its tiles through every panel, then D^-1 into the
+// staging rows.  Leaves after a bad pivot.
+template <int NT>
+__device__ __forceinline__ void gjt_update(const GJArgs& j, GJShared<NT>& S, int w, int u, int lane) {
+    using P = GJT<NT>;
+    constexpr int CT = P::CT, NU = P::NU, LS = P::LS, PS = P::PS;
+    static_assert(CT == 2, "two column tiles per wave");
+    const int li = lane & 15, lg = lane >> 4;
+    const int n = j.n, np = (n + 15) >> 4;
+    f64x4 acc[NT][CT];
+    if (j.mode == QSL_FP64) gjt_load<NT>((const double*)j.C + (size_t)w * 5 * n * n, n, u, lane, acc);
+    else gjt_load<NT>((const float*)j.C + (size_t)w * 5 * n * n, n, u, lane, acc);
+    // pivot-row entries of this wave's columns, [k][16 ct + 4 (e % 4) + e / 4]
+    double* pr = S.main + 3 * 16 * LS + u * 16 * PS;
+    double* Xw = S.X() + lg * LS + li;
+    // column tile ct to the panel wave
+    auto stage_tile = [&](auto ctc, int p) __attribute__((always_inline)) {
+        constexpr int ct = decltype(ctc)::value;
+#pragma unroll
+        for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Xw[4 * r * LS + 16 * ti] = acc[ti][ct][r];
+        if (lane == 0) flag_store(&S.xready, p);
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    if (u == 0) stage_tile(I0{}, 0);
+#pragma unroll 1
+    for (int p = 0; p < np; ++p) {
+        __syncthreads();  // F of panel p is published; every update of panel p - 1 is done
+        if (S.bad) return;
+        const double* Fp = S.F(p);
+        const double* L = Fp + lg * LS + li;
+        // the panel's columns come back as their own steps left them
+        if (p % NU == u) {
+            static_for<0, CT>([&](auto ctc) __attribute__((always_inline)) {
+                constexpr int ct = decltype(ctc)::value;
+                if (p == u + NU * ct) {
+#pragma unroll
+                    for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[ti][ct][r] = Xw[4 * r * LS + 16 * ti];
+                }
+            });
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            if (lane == 0) flag_store(&S.xfree, p);
+        }
+        // the pivot rows' entries of this wave's columns
+        {
+            const uint4 o4 = *(const uint4*)S.ord[li];
+            const uint32_t ov[4] = {o4.x, o4.y, o4.z, o4.w};
+#pragma unroll
+            for (int ti = 0; ti < NT; ++ti) {
+                const uint32_t k = ((ov[ti >> 2] >> (8 * (ti & 3))) & 0xffu) - (uint32_t)(16 * p + 1);
+                if (k < 16u) {
+                    f64x4* pk = (f64x4*)(pr + k * PS + 4 * lg);
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct) pk[4 * ct] = acc[ti][ct];
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        // w from them: lane (lg, li) of register b holds step 4 b + lg of
+        // column li, which is also how the products read it as an operand;
+        // one product per step m, its multipliers F_m[p_k] masked to the rows
+        // k > m (entries of an own column up to its own step start and stay 0)
+        const int prow = S.perm[16 * p + li];
+        double* pw = pr + lg * PS + 4 * (li & 3) + (li >> 2);
+        auto solve = [&](int ct) __attribute__((always_inline)) {
+            const bool own = p == u + NU * ct;
+            f64x4 wv;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const double x = pw[4 * b * PS + 16 * ct];
+                wv[b] = own && 4 * b + lg <= li ? 0.0 : x;
+            }
+            static_for<0, 4>([&](auto bc) __attribute__((always_inline)) {
+                constexpr int b = decltype(bc)::value;
+                const double nb = Fp[(4 * b + lg) * LS + prow];
+                static_for<0, (b == 3 ? 3 : 4)>([&](auto kc) __attribute__((always_inline)) {
+                    constexpr int kk = decltype(kc)::value;
+                    const double a = lg == kk && li > 4 * b + kk ? nb : 0.0;
+                    wv = __builtin_amdgcn_mfma_f64_16x16x4f64(a, wv[b], wv, 0, 0, 0);
+                });
+            });
+#pragma unroll
+            for (int b = 0; b < 4; ++b) pw[4 * b * PS + 16 * ct] = wv[b];
+        };
+        const bool next = p + 1 < np && (p + 1) % NU == u, second = p + 1 >= NU;
+        // the next panel's columns in a pass of their own first, handed over
+        // before the rest (the wave four further on runs on the same SIMD
+        // and lets them pass)
+        if (next) __builtin_amdgcn_s_setprio(2);
+        if (NU > 4 && p + 1 < np && (p + 1) % NU == (u ^ 4)) flag_wait(&S.xready, p + 1);
+#pragma unroll 1
+        for (int pass = next ? 0 : 1; pass < 2; ++pass) {
+            const bool do0 = pass == 0 ? !second : u != p + 1;
+            const bool do1 = pass == 0 ? second : u + NU < NT && u + NU != p + 1;
+#pragma unroll 1
+            for (int ct = 0; ct < CT; ++ct)
+                if (ct == 0 ? do0 : do1) solve(ct);
+            __builtin_amdgcn_wave_barrier();
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+#pragma unroll 1
+            for (int kk = 0; kk < 4; ++kk) {
+                const double* Lk = L + 4 * kk * LS;
+                if (do0) {
+                    const double a = pw[4 * kk * PS];
+#pragma unroll
+                    for (int ti = 0; ti < NT; ++ti)
+                        acc[ti][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Lk[16 * ti], acc[ti][0], 0, 0, 0);
+                }
+                if (do1) {
+                    const double a = pw[4 * kk * PS + 16];
+#pragma unroll
+                    for (int ti = 0; ti < NT; ++ti)
+                        acc[ti][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Lk[16 * ti], acc[ti][1], 0, 0, 0);
+                }
+            }
+            if (pass == 0) {
+                flag_wait(&S.xfree, p);
+                if (second) stage_tile(I1{}, p + 1);
+                else stage_tile(I0{}, p + 1);
+                __builtin_amdgcn_s_setprio(0);
+            }
+        }
     }
-    double* Dw = Dinv + (size_t)w * nn;
-    if (singular) {
+    __syncthreads();  // the panels are no longer read
+    const uint4 o4 = *(const uint4*)S.ord[li];
+    const uint32_t ov[4] = {o4.x, o4.y, o4.z, o4.w};
+    auto step_of = [&](int ti) __attribute__((always_inline)) { return (int)((ov[ti >> 2] >> (8 * (ti & 3))) & 0xffu) - 1; };
+    // D^-1[k][p_j] = M[p_k][j] / pivot(k), staged QC rows at a time.  The
+    // pivot entries were left at pv during the elimination (the pivot row is
+    // never scaled); their value in the scaled representation is 1, and later
+    // updates of them only added terms: M[p_k][k] += 1 - pv_k
+    int pd[CT][4];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int e = 16 * (u + NU * ct) + lg + 4 * r;
+            pd[ct][r] = e < n ? S.perm[e] : P::NP;  // (past n: a spare column)
+        }
+#pragma unroll 1
+    for (int q0 = 0; q0 < n; q0 += P::QC) {
+#pragma unroll
+        for (int ti = 0; ti < NT; ++ti) {
+            const int k = step_of(ti);
+            if ((uint32_t)(k - q0) < (uint32_t)P::QC) {
+                const double pv = S.pvs[k], rs = 1.0 / pv;
+                double* to = S.main + (k - q0) * P::SS;
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const double d = 16 * (u + NU * ct) + lg + 4 * r == k ? 1.0 - pv : 0.0;
+                        const double x = acc[ti][ct][r] + d;
+                        to[pd[ct][r]] = x * rs;
+                    }
+            }
+        }
+        gjt_copy_out<NT>(j, S, w, q0, u, lane);
+    }
+}
+
+template <int NT>
+__device__ __forceinline__ void gjt_body(const GJArgs& j, int w) {
+    using P = GJT<NT>;
+    __shared__ __align__(32) GJShared<NT> S;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid < 64) ((uint32_t*)S.ord)[tid] = 0u;
+    if (tid == 0) { S.xready = S.xfree = -1; S.bad = 0; }
+    __syncthreads();
+    if (wave == P::NU) {
+        gjt_panels<NT>(j, S, w, lane);
+        if (!S.bad) {
+            __syncthreads();
+            for (int q0 = 0; q0 < j.n; q0 += P::QC) gjt_copy_out<NT>(j, S, w, q0, wave, lane);
+        }
+    } else {
+        gjt_update<NT>(j, S, w, wave, lane);
+    }
+    if (S.bad) {
         // undefined inverse: NaN, log|det| = -inf, sign = 0
-        for (size_t q = tid; q < nn; q += NT) Dw[q] = __longlong_as_double(0x7ff8000000000000ll);
+        const size_t nn = (size_t)j.n * j.n;
+        double* Dw = j.Dinv + (size_t)w * nn;
+        for (size_t q = tid; q < nn; q += P::THREADS) Dw[q] = __longlong_as_double(0x7ff8000000000000ll);
         if (tid == 0) {
-            if (logdet) logdet[2 * w + spin] = s_flag == 1 ? -INFINITY : __longlong_as_double(0x7ff8000000000000ll);
-            if (sign) sign[2 * w + spin] = 0;
-            if (status) atomicOr(status + w, s_flag == 1 ? QSL_STATUS_SINGULAR : QSL_STATUS_NONFINITE);
+            if (j.logdet) j.logdet[2 * (size_t)w + j.spin] = S.bad == 1 ? -INFINITY : __longlong_as_double(0x7ff8000000000000ll);
+            if (j.sign) j.sign[2 * (size_t)w + j.spin] = 0;
+            if (j.status) atomicOr(j.status + w, S.bad == 1 ? QSL_STATUS_SINGULAR : QSL_STATUS_NONFINITE);
         }
-        return;
-    }
-    // log|det| = sum log|pivot|; sign = sign(permutation) prod sign(pivot),
-    // the permutation's sign from the parity of its inversions
-    {
-        double ld = 0.0;
-        int neg = 0;
-        if (tid < n) {
-            ld = log(fabs(rowpiv[tid]));
-            neg = rowpiv[tid] < 0.0;
-            const int pa = perm[tid];
-            for (int b2 = tid + 1; b2 < n; ++b2) neg += perm[b2] < pa;
-        }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            ld += __shfl_xor(ld, o);
-            neg += __shfl_xor(neg, o);
-        }
-        if (lane == 0) { red_ld[wave] = ld; red_neg[wave] = neg; }
-    }
-    for (int k = tid; k < n; k += NT) invp[perm[k]] = k;
-    __syncthreads();
-    if (tid == 0) {
-        double ld = 0.0;
-        int neg = 0;
-        for (int v = 0; v < NT / 64; ++v) { ld += red_ld[v]; neg += red_neg[v]; }
-        if (logdet) logdet[2 * w + spin] = ld;
-        if (sign) sign[2 * w + spin] = (neg & 1) ? -1 : 1;
-        if (status && !isfinite(ld)) atomicOr(status + w, QSL_STATUS_NONFINITE);
-    }
-    // the pivot entries were left at pv during the elimination (the pivot row
-    // is never scaled); their value in the scaled representation is 1, and
-    // later updates of them only added terms: M[p_k][k] += 1 - pv_k
-    int ec[CPW];  // D column of each register column
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) ec[c] = 16 * (c + rot < CPW ? c + rot : c + rot - CPW) + 2 * wave + h;
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const int i = li + 32 * r;
-        if (i >= n) continue;
-        const int kp = invp[i];
-#pragma unroll
-        for (int c = 0; c < CPW; ++c)
-            if (ec[c] == kp) M[r][c] += 1.0 - rowpiv[i];
-    }
-    // D^-1[invp[i]][perm[e]] = M[i][e] / pivot(i), staged QC rows at a time
-    int rowi[RPL];
-    double rs[RPL];
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const int i = li + 32 * r;
-        rowi[r] = i < n ? invp[i] : -1;
-        rs[r] = i < n ? 1.0 / rowpiv[i] : 0.0;
-    }
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) ec[c] = ec[c] < n ? perm[ec[c]] : -1;  // destination column
-    for (int q0 = 0; q0 < n; q0 += QC) {
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            const int rr = rowi[r] - q0;
-            if (rr >= 0 && rr < QC) {
-#pragma unroll
-                for (int c = 0; c < CPW; ++c)
-                    if (ec[c] >= 0) stage[rr][ec[c]] = M[r][c] * rs[r];
-            }
-        }
-        __syncthreads();
-        const int rows = min(QC, n - q0);
-        for (int q = tid; q < rows * n; q += NT) {
-            const int rr = q / n, cc = q % n;
-            gmem(Dw)[(size_t)(q0 + rr) * n + cc] = stage[rr][cc];
-        }
-        __syncthreads();
     }
 }
 
-template <int RPL, int CPW, typename Tin>
-__global__ __launch_bounds__(512) void gjh2_kernel(Job j) {
-    gjh2_body<RPL, CPW, Tin>(j, blockIdx.x);
-}
-template <int RPL, int CPW, typename Tin>
-__global__ __launch_bounds__(512) void gjh2_batched(const Job* jobs, const int* prefix, int njobs) {
-    batch_block(jobs, prefix, njobs, [&](const Job& jj, int bx, int, int) { gjh2_body<RPL, CPW, Tin>(jj, bx); });
-}
-template <int NWV, int RPL, int CPW, typename Tin>
-__global__ __launch_bounds__(NWV * 64) void gj_kernel(Job j) {
-    gj_body<NWV, RPL, CPW, Tin>(j, blockIdx.x);
-}
-
-template <int NWV, int RPL, int CPW, typename Tin>
-__global__ __launch_bounds__(NWV * 64) void gj_batched(const Job* jobs, const int* prefix, int njobs) {
-    batch_block(jobs, prefix, njobs, [&](const Job& j, int bx, int, int) { gj_body<NWV, RPL, CPW, Tin>(j, bx); });
+// One workgroup per matrix: of the Job described by value, or (jobs) of a
+// batched launch.
+template <int NT>
+__global__ __launch_bounds__(GJT<NT>::THREADS, GJT<NT>::WPE) void gjt_kernel(GJArgs a, const Job* jobs, const int* prefix, int njobs) {
+    int w = blockIdx.x;
+    if (jobs) {
+        const int ji = __builtin_amdgcn_readfirstlane(find_job(prefix, njobs, w));
+        w -= prefix[ji];
+        a = gj_args(jobs[ji]);
+    }
+    gjt_body<NT>(a, w);
 }
 
 __global__ void empty_spin_kernel(int64_t W, int spin, double* logdet, int8_t* sign) {
@@ -740,34 +715,24 @@ __global__ void empty_spin_kernel(int64_t W, int spin, double* logdet, int8_t* s
     }
 }
 
-// Variants by matrix size: register-resident 0: n <= 32, 1: <= 64,
-// 2: <= 128, 3: <= 224; 4: blocked, n <= 1024.
-int gj_variant(int n) { return gj_blocked(n) ? 4 : n <= 32 ? 0 : n <= 64 ? 1 : n <= 128 ? 2 : 3; }
-int gj_threads(int v) { return v == 0 ? 128 : v == 1 ? 256 : 512; }
+// Variants by matrix size: 0 .. 13 register-resident, n <= 16 (v + 1);
+// GJ_V_BLOCKED: blocked, n <= 1024.
+int gj_variant(int n) { return gj_blocked(n) ? GJ_V_BLOCKED : (std::max(n, 1) - 1) / 16; }
 int gj_job_variant(const Job& j) {
     const int v = gj_variant(j.n);
-    return v == 4 ? 4 : std::min(3, v + std::max(0, j.gj_bias));
+    return v == GJ_V_BLOCKED ? v : std::min(GJ_V_BLOCKED - 1, v + std::max(0, j.gj_bias));
 }
 
-template <typename Tin>
-static hipError_t gj_dispatch(const Job& j, int v, bool batched, const Job* jobs, const int* prefix, int njobs,
-                              int grid, hipStream_t st) {
-    const dim3 g((unsigned)(batched ? grid : j.W));
-#define QSL_GJ(NWV, RPL, CPW)                                                                                   \
-    do {                                                                                                        \
-        if (batched) gj_batched<NWV, RPL, CPW, Tin><<<g, NWV * 64, 0, st>>>(jobs, prefix, njobs);         \
-        else gj_kernel<NWV, RPL, CPW, Tin><<<g, NWV * 64, 0, st>>>(j);                                          \
-    } while (0)
+static hipError_t gj_dispatch(const GJArgs& a, int v, const Job* jobs, const int* prefix, int njobs, int grid,
+                              hipStream_t st) {
     switch (v) {
-        case 0: QSL_GJ(2, 1, 16); break;
-        case 1: QSL_GJ(4, 1, 16); break;
-        case 2: QSL_GJ(8, 2, 16); break;
-        default:
-            if (batched) gjh2_batched<7, 14, Tin><<<g, 512, 0, st>>>(jobs, prefix, njobs);
-            else gjh2_kernel<7, 14, Tin><<<g, 512, 0, st>>>(j);
-            break;
-    }
+#define QSL_GJ(NT)                                                                                        \
+    case NT - 1: gjt_kernel<NT><<<(unsigned)grid, GJT<NT>::THREADS, 0, st>>>(a, jobs, prefix, njobs); break;
+        QSL_GJ(1) QSL_GJ(2) QSL_GJ(3) QSL_GJ(4) QSL_GJ(5) QSL_GJ(6) QSL_GJ(7)
+        QSL_GJ(8) QSL_GJ(9) QSL_GJ(10) QSL_GJ(11) QSL_GJ(12) QSL_GJ(13) QSL_GJ(14)
 #undef QSL_GJ
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
@@ -781,21 +746,17 @@ hipError_t launch_gj(const Job& j0, hipStream_t st) {
     }
     if (j.n > GJ_NMAX) return hipErrorInvalidValue;
     const int v = gj_job_variant(j);
-    if (v == 4) return launch_gjb(j, st);
-    if (j.mode == QSL_FP64) return gj_dispatch<double>(j, v, false, nullptr, nullptr, 0, 0, st);
-    return gj_dispatch<float>(j, v, false, nullptr, nullptr, 0, 0, st);
+    if (v == GJ_V_BLOCKED) return launch_gjb(j, st);
+    return gj_dispatch(gj_args(j), v, nullptr, nullptr, 0, (int)j.W, st);
 }
 
 // One batched launch of GJ variant v over Jobs whose n all fit it (the
 // plan launches each variant present in its batch once; the blocked
-// variant 4 is a sequence of launches over panels, see qsl_gjb.hip).
-hipError_t launch_gj_batched(int mode, int v, const Job* jobs, const int* prefix, int njobs, int grid,
-                             hipStream_t st) {
-    if (v < 0 || v > 3) return hipErrorInvalidValue;
+// variant is a sequence of launches over panels, see qsl_gjb.hip).
+hipError_t launch_gj_batched(int v, const Job* jobs, const int* prefix, int njobs, int grid, hipStream_t st) {
+    if (v < 0 || v >= GJ_V_BLOCKED) return hipErrorInvalidValue;
     if (grid <= 0) return hipSuccess;
-    Job dummy{};
-    if (mode == QSL_FP64) return gj_dispatch<double>(dummy, v, true, jobs, prefix, njobs, grid, st);
-    return gj_dispatch<float>(dummy, v, true, jobs, prefix, njobs, grid, st);
+    return gj_dispatch(GJArgs{}, v, jobs, prefix, njobs, grid, st);
 }
 
 }  // namespace qsl

@@ -514,17 +514,16 @@ hipError_t launch_contract_batched(int mode, int tile, unsigned* queue, const Jo
 int contract_per_cu(int mode, int tile);
 // Gauss-Jordan inversion, log|det| and sign (one block per matrix; the
 // block shape depends on n, so a batched launch serves one variant).
+constexpr int GJ_V_BLOCKED = 14;   // the variants below it are register-resident, n <= 16 (v + 1)
 int gj_variant(int n);
-int gj_threads(int v);
-int gj_job_variant(const Job& j);  // gj_variant(n) + gj_bias, clamped; 4 = blocked
-// Blocked inversion (variant 4, 224 < n <= 1024): the launch sequence of one
+int gj_job_variant(const Job& j);  // gj_variant(n) + gj_bias, clamped
+// Blocked inversion (GJ_V_BLOCKED, 224 < n <= 1024): the launch sequence of one
 // Job, or of the Jobs of a plan (prefix counts matrices, nmax = largest n).
 hipError_t launch_gjb(const Job& j, hipStream_t st);
 hipError_t launch_gjb_batched(int mode, const Job* jobs, const int* prefix, int njobs, int matrices, int nmax,
                               hipStream_t st);
 hipError_t launch_gj(const Job& j, hipStream_t st);
-hipError_t launch_gj_batched(int mode, int v, const Job* jobs, const int* prefix, int njobs, int grid,
-                             hipStream_t st);
+hipError_t launch_gj_batched(int v, const Job* jobs, const int* prefix, int njobs, int grid, hipStream_t st);
 // Row length of the FP32 G of the dA by electron: whole blocks of 224 MOs.
 __host__ __device__ inline int g32_ld(int n) { return (n + ADJ_MB - 1) / ADJ_MB * ADJ_MB; }
 // G = g D^-1 in FP32 (Job.g32) for walkers bound without the epilogue.

@@ -21,11 +21,8 @@ namespace qsl {
 enum Phase {
     PH_SCREEN = 0,   // per-tile window lists (forward; reused by the adjoint)
     PH_CONTRACT,     // AO evaluation + the five products
-    PH_GJ0,          // Gauss-Jordan, one phase per block shape
-    PH_GJ1,
-    PH_GJ2,
-    PH_GJ3,
-    PH_GJ4,          // blocked (n > 224)
+    PH_GJ0,          // Gauss-Jordan, one phase per variant
+    PH_GJB = PH_GJ0 + GJ_V_BLOCKED,  // blocked (n > 224)
     PH_EPILOGUE,     // drift and Laplacian
     PH_EPI_G,        // drift and Laplacian with the split-BF16 G^T (BF16X3 with dA)
     PH_DR,           // dR = g drift (drift bound)
@@ -382,17 +379,17 @@ static qsl_status enqueue(qsl_plan* p, hipStream_t st) {
                                              (int)C.jobs.size(), grid, st)) != hipSuccess)
                 return hip_fail(e, "contraction kernel");
         }
-        for (int v = 0; v <= 4; ++v) {
+        for (int v = 0; v <= GJ_V_BLOCKED; ++v) {
             auto& G = p->ph[PH_GJ0 + v];
             if (!G.blocks()) continue;
             ProfScope ps("gauss_jordan", st);
-            if (v == 4) {
+            if (v == GJ_V_BLOCKED) {
                 int nmax = 0;
                 for (const Job& j : G.jobs) nmax = std::max(nmax, j.n);
-                e = launch_gjb_batched(mode, dev_jobs(p, PH_GJ4), dev_prefix(p, PH_GJ4), (int)G.jobs.size(),
+                e = launch_gjb_batched(mode, dev_jobs(p, PH_GJB), dev_prefix(p, PH_GJB), (int)G.jobs.size(),
                                        G.blocks(), nmax, st);
             } else {
-                e = launch_gj_batched(mode, v, dev_jobs(p, PH_GJ0 + v), dev_prefix(p, PH_GJ0 + v),
+                e = launch_gj_batched(v, dev_jobs(p, PH_GJ0 + v), dev_prefix(p, PH_GJ0 + v),
                                       (int)G.jobs.size(), G.blocks(), st);
             }
             if (e != hipSuccess) return hip_fail(e, "inversion kernel");
@@ -410,7 +407,7 @@ static qsl_status enqueue(qsl_plan* p, hipStream_t st) {
             ProfScope ps(contract_name(mode), st);
             if ((e = launch_contract(j, st)) != hipSuccess) return hip_fail(e, "contraction kernel");
         }
-        for (int v = 0; v <= 4; ++v)
+        for (int v = 0; v <= GJ_V_BLOCKED; ++v)
             for (const Job& j : p->ph[PH_GJ0 + v].jobs) {
                 ProfScope ps("gauss_jordan", st);
                 if ((e = launch_gj(j, st)) != hipSuccess) return hip_fail(e, "inversion kernel");
@@ -986,7 +983,7 @@ static qsl_status autotune_run(qsl_plan* p, hipStream_t st, const std::string& k
     std::vector<qsl_tuning> cands;
     for (int bt = 1; bt >= 0; --bt)
         for (int gb = 0; gb <= 1; ++gb) {
-            if (gb && gj_variant(nmax) >= 3) continue;  // no larger block shape
+            if (gb && gj_variant(nmax) >= GJ_V_BLOCKED - 1) continue;  // no larger block shape
             const int groups[] = {0, 16, 32, 64, 128, 256, 512, 1024};
             for (int g : groups) {
                 if (!any_bwd && g) continue;
