@@ -14,7 +14,8 @@
 // n is skipped.
 //
 // Precision modes:
-//   FP64   AO eval FP64, v_mfma_f64_16x16x4f64, 64 MOs per workgroup.
+//   FP64   AO eval FP64 over the tile's surviving slots, v_mfma_f64_16x16x4f64,
+//          up to 128 or 256 MOs per workgroup.
 //   FP32   AO eval FP32, over the tile's surviving slots rather than whole
 //          windows (below), 256 MOs per workgroup; the products by default
 //          as six v_mfma_f32_32x32x16_bf16 products of exact three-way bf16
@@ -34,22 +35,21 @@ typedef __attribute__((ext_vector_type(4))) double f64x4;
 
 constexpr int CT_WAVES = 4;
 
-template <int MODE>
+// Split BF16 workgroup.
 struct CT {
     // windows per chunk, MO columns per wave, MO columns per workgroup
-    static constexpr int KW = MODE == QSL_FP64 ? 4 : 8;
+    static constexpr int KW = 8;
     static constexpr int KC = KW * WIN;
-    static constexpr int NBW = MODE == QSL_FP64 ? 16 : 32;
-    static constexpr int MSUB = MODE == QSL_FP64 ? 1 : 2;  // MO sub-blocks per wave
+    static constexpr int NBW = 32;
+    static constexpr int MSUB = 2;  // MO sub-blocks per wave
     static constexpr int NSB = CT_WAVES * NBW;      // MOs per sub-block
     static constexpr int NB = MSUB * NSB;
     static constexpr int THREADS = CT_WAVES * 64;
     // AO evaluation: slots of one window per thread (8, or 4 when the
     // workgroup has twice as many threads as (electron, window) pairs)
     static constexpr int SPT = THREADS >= 2 * TE * KW ? WIN / 2 : WIN;
-    using T = typename std::conditional<MODE == QSL_FP64, double, float>::type;
     // LDS row stride (elements) of one electron's chunk of B
-    static constexpr int LD = MODE == QSL_BF16X3 ? KC + 8 : (MODE == QSL_FP32 ? KC + 4 : KC + 2);
+    static constexpr int LD = KC + 8;
 };
 
 // ---------------------------------------------------------------- FP32
@@ -534,31 +534,321 @@ __device__ __forceinline__ void contract_f32_body(const Job& j, int bx, int by, 
     }
 }
 
-template <int MODE>
-__device__ __forceinline__ void contract_body(const Job& j, int bx, int by, int tid_in) {
-    if constexpr (MODE == QSL_FP32) {
-        contract_f32_body<0>(j, bx, by, tid_in);
-    } else {
+// ---------------------------------------------------------------- FP64
+// As FP32, the tile's surviving slots (not whole windows) are the K
+// dimension: the windows' filter fills a ring of slot indices, chunks of 32
+// slots are evaluated into LDS and contracted with v_mfma_f64_16x16x4f64.
+// A slot left out adds exact zeros, and the matrix unit adds its four
+// products to an accumulator in order, each with one rounding, so C does not
+// depend on the grouping of the slots: it is the sum over the survivors in
+// ascending slot order.
+// Wave w takes the half w % 2 of the tile's 32 electrons and the blocks of 16
+// MOs w / 2, w / 2 + NW / 2, .. (at most four: 160 accumulator registers), so
+// its blocks share the AO operands; NW = 4 waves hold up to 128 MOs, 8 up to
+// 256.  The AO evaluation runs once per workgroup: with 64 MOs of whole
+// windows per workgroup (before) it ran 4 times at 217 MOs, 14 times at 866.
+// Measured, before and now: 434 electrons x 1024 walkers 20.3 and 9.5 ms (the
+// products alone 6.9, 4.9 at the matrix rate; the evaluation 2.6), 1731 x 96
+// 21.1 and 11.6 ms, 158 x 1000 2.45 and 1.25 ms.  Without gain: two chunk
+// buffers, evaluating the next chunk beside the products (10.3 ms: it spills).
+template <int NW>
+struct F64T {
+    static constexpr int UMAX = 4;                      // MO blocks per wave
+    static constexpr int NB = 16 * UMAX * (NW / 2);     // MOs per workgroup
+    static constexpr int THREADS = NW * 64;
+    static constexpr int KC = 32;                       // slots per chunk
+    static constexpr int LD = KC + 2;
+    static constexpr int EPT = TE / (THREADS / KC);     // electrons per thread of the evaluation
+};
+
+// rec_values of one slot, its record's first primitives in registers.
+struct SlotR64 {
+    double x, y, z, f;
+    double ex[3], c[3];
+    int pw, np;
+    __device__ __forceinline__ void load(const SlotRec64* r) {
+        typedef __attribute__((ext_vector_type(2))) double f64x2;
+        const f64x2 a = *gmem((const f64x2*)&r->pos[0]), b = *gmem((const f64x2*)&r->pos[2]);
+        const f64x2 e0 = *gmem((const f64x2*)&r->ex[0]), e1 = *gmem((const f64x2*)&r->ex[2]);
+        const f64x2 c0 = *gmem((const f64x2*)&r->c64[0]), c1 = *gmem((const f64x2*)&r->c64[2]);
+        typedef __attribute__((ext_vector_type(2))) int i32x2;
+        const i32x2 t = *gmem((const i32x2*)&r->pw);
+        x = a.x; y = a.y; z = b.x; f = b.y;
+        ex[0] = e0.x; ex[1] = e0.y; ex[2] = e1.x;
+        c[0] = c0.x; c[1] = c0.y; c[2] = c1.x;
+        pw = t.x; np = t.y;
+    }
+};
+static_assert(offsetof(SlotRec64, pos) == 0 && offsetof(SlotRec64, f64) == 24 && offsetof(SlotRec64, np) == offsetof(SlotRec64, pw) + 4,
+              "slot record layout read by SlotR64::load");
+
+__device__ __forceinline__ void slot_values64(const SlotR64& r, const SlotRec64* __restrict__ rec, double T_thr,
+                                              const double p[3], double v[5], bool& tie) {
+    const double X = p[0] - r.x, Y = p[1] - r.y, Z = p[2] - r.z;
+    const double r2 = dist2_exact(X, Y, Z);
+    const double tieb = 1e-12 * T_thr;
+    double g = 0, g1 = 0, g2 = 0;
+    auto prim = [&](double gk, double ck) __attribute__((always_inline)) {
+        const double t = mul_exact(gk, r2);
+        tie |= fabs(t - T_thr) <= tieb;
+        if (t <= T_thr) {
+            const double ek = ck * exp_t(-t);
+            g += ek;
+            g1 += -2.0 * gk * ek;
+            g2 += ek * (4.0 * gk * gk * r2 - 6.0 * gk);
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        if (k < r.np) prim(r.ex[k], r.c[k]);
+#pragma unroll 1
+    for (int k = 3; k < r.np; ++k) prim(gmem(rec)->ex[k], gmem(rec)->c64[k]);
+    const int a = r.pw & 15, b = (r.pw >> 4) & 15, c = (r.pw >> 8) & 15, l = (r.pw >> 12) & 15;
+    double px, ddx, d2x, py, ddy, d2y, pz, ddz, d2z;
+    axis_pow(a, X, px, ddx, d2x);
+    axis_pow(b, Y, py, ddy, d2y);
+    axis_pow(c, Z, pz, ddz, d2z);
+    const double f = r.f;
+    const double fyz = f * py * pz, fxz = f * px * pz, fxy = f * px * py;
+    const double P = fyz * px;
+    const double pg1 = P * g1;
+    v[0] = P * g;
+    v[1] = fyz * ddx * g + pg1 * X;
+    v[2] = fxz * ddy * g + pg1 * Y;
+    v[3] = fxy * ddz * g + pg1 * Z;
+    v[4] = (d2x * fyz + d2y * fxz + d2z * fxy) * g + (double)(2 * l) * pg1 + P * g2;
+}
+
+// The filter shared by the FP32 and FP64 forms is written out in each: the
+// FP32 ring also carries the MO-block masks.
+template <int NW>
+__device__ __forceinline__ void contract_f64_body(const Job& j, int bx, int by, int tid_in) {
+    using P = F64T<NW>;
+    constexpr int KC = P::KC, LD = P::LD, UMAX = P::UMAX;
+    const DevSys& s = j.s;
+    const int spin = j.spin, n = j.n, nmo = j.mo.n, ldn = j.mo.ldn;
+    const int64_t W = j.W;
+    const double* __restrict__ R = j.R;
+    const double* __restrict__ AT64 = j.mo.AT64;
+    const SlotRec* __restrict__ srec = s.slot_rec;
+    const SlotRec64* __restrict__ srec64 = s.slot_rec64;
+    uint32_t* __restrict__ status = j.status;
+
+    __shared__ double epos[TE][3];
+    __shared__ double B[5 * TE * LD];
+    __shared__ int ring[F32_RING];
+    __shared__ int ringo[F32_RING];  // slot * ldn: the slot's coefficient row
+    __shared__ uint32_t wmask[F32_BATCH];
+    __shared__ int s_tail;
+    __shared__ int wt[TE];  // the tile's walkers (Job.wperm order)
+
+    const int tile = bx;
+    const int nblk = (nmo + 15) >> 4, per = (nblk + j.gy - 1) / j.gy;  // MO blocks of all, of a workgroup
+    const int b0 = by * per, mine = min(per, nblk - b0);
+    const int wbk = walker_blocks(W);
+    const int eidx = tile / wbk;
+    const int w0 = (tile % wbk) * TE;
+    const int ne = (int)min<int64_t>(TE, W - w0);
+    const int N = s.n_up + s.n_dn;
+    const int eoff = spin ? s.n_up : 0;
+    const int tid = tid_in, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const double Tscr = s.T;
+
+    if (tid < TE * 3) {
+        const int e = tid / 3, k = tid % 3;
+        epos[e][k] = e < ne ? R[((size_t)walker_of(j.wperm, W, eidx, w0 + e) * N + eoff + eidx) * 3 + k] : 0.0;
+    }
+    if (tid < TE) wt[tid] = tid < ne ? (int)walker_of(j.wperm, W, eidx, w0 + tid) : 0;
+    if (tid == 0) s_tail = 0;
+    const int nwin = j.nwin[tile];
+    const int* __restrict__ wins = j.win + (size_t)tile * s.n_win;
+    const int half = wave & 1;
+    // this wave's blocks: (wave >> 1) + (NW / 2) q < mine
+    const int nq = max(0, min(UMAX, (mine - (wave >> 1) + NW / 2 - 1) / (NW / 2)));
+    const double* __restrict__ Aw = AT64 + 16 * (b0 + (wave >> 1)) + li;
+    int boff[UMAX];
+#pragma unroll
+    for (int q = 0; q < UMAX; ++q) boff[q] = q < nq ? 16 * (NW / 2) * q : 0;
+    f64x4 acc[UMAX][5];
+#pragma unroll
+    for (int q = 0; q < UMAX; ++q)
+#pragma unroll
+        for (int d = 0; d < 5; ++d) acc[q][d] = f64x4{0, 0, 0, 0};
+    uint32_t tiebits = 0;  // near ties seen by this thread, one bit per electron it evaluates
+    bool ftie = false;     // a near tie in the slot filter for electron lane % 32
+    __syncthreads();
+
+    int tail = 0, w1 = 0;
+    // ---- filter: windows w1 .. w1 + 31 of the tile's list
+    auto filter = [&]() __attribute__((always_inline)) {
+        const int e = lane & (TE - 1);
+#pragma unroll
+        for (int it = 0; it < F32_BATCH / (2 * NW); ++it) {
+            const int wl = it * 2 * NW + wave * 2 + (lane >> 5);
+            const int q = w1 + wl < nwin ? wins[w1 + wl] : -1;
+            uint32_t m = 0;
+            if (q >= 0 && e < ne) {
+                const SlotRec* rq = srec + (size_t)q * WIN;
+                const double r2 = dist2_exact(epos[e][0] - rq->pos[0], epos[e][1] - rq->pos[1],
+                                              epos[e][2] - rq->pos[2]);
+#pragma unroll
+                for (int jj = 0; jj < WIN; ++jj) {
+                    const double t = mul_exact(rq[jj].gmin, r2);
+                    if (t <= Tscr) m |= 1u << jj;
+                    else ftie |= t - Tscr <= 1e-12 * Tscr;
+                }
+            }
+            uint32_t wm = 0;
+#pragma unroll
+            for (int jj = 0; jj < WIN; ++jj) {
+                const uint64_t bal = __ballot((m >> jj) & 1u);
+                const uint32_t hb = (uint32_t)(lane < 32 ? bal : (bal >> 32));
+                wm |= (hb != 0u ? 1u : 0u) << jj;
+            }
+            if ((lane & 31) == 0) wmask[wl] = wm;
+        }
+        __syncthreads();
+        if (wave == 0 && lane < F32_BATCH) {
+            const uint32_t m = w1 + lane < nwin ? wmask[lane] : 0u;
+            const int q = w1 + lane < nwin ? wins[w1 + lane] : 0;
+            const int c = __popc(m);
+            int x = c;  // inclusive prefix over the 32 windows
+#pragma unroll
+            for (int o = 1; o < 32; o <<= 1) {
+                const int y = __shfl_up(x, o, 32);
+                if (lane >= o) x += y;
+            }
+            int pos = tail + x - c;
+            for (uint32_t mm = m; mm; mm &= mm - 1) {
+                const int sl = q * WIN + __builtin_ctz(mm);
+                ring[pos & (F32_RING - 1)] = sl;
+                ringo[pos & (F32_RING - 1)] = sl * ldn;
+                ++pos;
+            }
+            if (lane == F32_BATCH - 1) s_tail = tail + x;
+        }
+        __syncthreads();
+        tail = s_tail;
+        w1 += F32_BATCH;
+    };
+    // ---- AO values of the chunk [head, head + 32) into LDS
+    auto evaluate = [&](int head) __attribute__((always_inline)) {
+        const int kk = tid & (KC - 1), eg = tid / KC;
+        const bool live = head + kk < tail;
+        const int slot = live ? ring[(head + kk) & (F32_RING - 1)] : 0;
+        // the last chunk: entries past the list become row 0 (the filter is
+        // done, nothing is appended after); their values are zero
+        if (!live && eg == 0) ringo[(head + kk) & (F32_RING - 1)] = 0;
+        SlotR64 r;
+        r.load(srec64 + slot);
+#pragma unroll 1
+        for (int i = 0; i < P::EPT; ++i) {
+            const int e = eg + (P::THREADS / KC) * i;
+            bool tie = false;
+            double v[5] = {0, 0, 0, 0, 0};
+            if (live && e < ne) {
+                const double p[3] = {epos[e][0], epos[e][1], epos[e][2]};
+                slot_values64(r, srec64 + slot, Tscr, p, v, tie);
+            }
+            tiebits |= (tie ? 1u : 0u) << i;
+#pragma unroll
+            for (int d = 0; d < 5; ++d) B[(d * TE + e) * LD + kk] = v[d];
+        }
+    };
+    // ---- products: k-step t takes chunk slots 4 t .. 4 t + 3; the next
+    // k-step's operands load during this one's products.  Every block is
+    // loaded, one past this wave's last as its first again: a load under a
+    // branch would have the products wait for all of them.
+    auto products = [&](int head) __attribute__((always_inline)) {
+        if (nq <= 0) return;
+        double bn[UMAX], an[5];
+        const double* Bh = B + (16 * half + li) * LD + lg;
+        auto load = [&](int t) __attribute__((always_inline)) {
+            const int row = ringo[(head + 4 * t + lg) & (F32_RING - 1)];
+#pragma unroll
+            for (int q = 0; q < UMAX; ++q) bn[q] = gmem(Aw)[row + boff[q]];
+#pragma unroll
+            for (int d = 0; d < 5; ++d) an[d] = Bh[d * TE * LD + 4 * t];
+        };
+        load(0);
+#pragma unroll 2
+        for (int t = 0; t < KC / 4; ++t) {
+            double bq[UMAX], aq[5];
+#pragma unroll
+            for (int q = 0; q < UMAX; ++q) bq[q] = bn[q];
+#pragma unroll
+            for (int d = 0; d < 5; ++d) aq[d] = an[d];
+            if (t + 1 < KC / 4) load(t + 1);
+#pragma unroll
+            for (int q = 0; q < UMAX; ++q) {
+                if (q >= nq) break;
+#pragma unroll
+                for (int d = 0; d < 5; ++d)
+                    acc[q][d] = __builtin_amdgcn_mfma_f64_16x16x4f64(aq[d], bq[q], acc[q][d], 0, 0, 0);
+            }
+        }
+    };
+    int head = 0;
+    while (w1 < nwin || head < tail) {
+        if (tail - head < KC && w1 < nwin) {
+            filter();
+            continue;
+        }
+        evaluate(head);
+        __syncthreads();
+        products(head);
+        __syncthreads();
+        head += KC;
+    }
+
+    // near ties flag the walkers of the electrons concerned
+    if (status) {
+        const int eg = tid / KC;
+        for (uint32_t tb = tiebits; tb; tb &= tb - 1) {
+            const int e = eg + (P::THREADS / KC) * __builtin_ctz(tb);
+            if (e < ne) atomicOr(status + wt[e], QSL_STATUS_NEAR_TIE);
+        }
+        if (ftie && (lane & 31) < ne) atomicOr(status + wt[lane & 31], QSL_STATUS_NEAR_TIE);
+    }
+    // ---- store C[w][d][e][mo]: result row lg + 4 r, column li
+    double* C = (double*)j.C;
+#pragma unroll
+    for (int q = 0; q < UMAX; ++q) {
+        if (q >= nq) break;
+        const int mo = 16 * (b0 + (wave >> 1) + (NW / 2) * q) + li;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int el = 16 * half + lg + 4 * r;
+            if (el < ne && mo < nmo) {
+#pragma unroll
+                for (int d = 0; d < 5; ++d) gmem(C)[(((size_t)wt[el] * 5 + d) * n + eidx) * nmo + mo] = acc[q][d][r];
+            }
+        }
+    }
+}
+
+// Split BF16: whole windows (8 slots, one k-group of an operand) per chunk.
+__device__ __forceinline__ void contract_bf16x3_body(const Job& j, int bx, int by, int tid_in) {
     const DevSys& s = j.s;
     const int spin = j.spin, n = j.n, nmo = j.mo.n, ldn = j.mo.ldn;
     const int64_t W = j.W;
     const double* __restrict__ R = j.R;
     const int* __restrict__ tile_nwin = j.nwin;
     const int* __restrict__ tile_win = j.win;
-    const double* __restrict__ AT64 = j.mo.AT64;
     const uint16_t* __restrict__ Ahi = j.mo.Ahi;
     const uint16_t* __restrict__ Alo = j.mo.Alo;
     void* __restrict__ Cout = j.C;
     uint32_t* __restrict__ status = j.status;
-    using P = CT<MODE>;
-    using T = typename P::T;
+    using P = CT;
+    using T = float;
     constexpr int KW = P::KW, KC = P::KC, LD = P::LD, SPT = P::SPT;
 
     __shared__ double epos[TE][3];
     __shared__ int wq[KW];
     // B chunk in LDS: [5][32 electrons][LD]
     constexpr int BELEMS = 5 * TE * LD;
-    __shared__ __attribute__((aligned(16))) unsigned char bbuf[MODE == QSL_BF16X3 ? 2 * BELEMS * 2 : BELEMS * sizeof(T)];
+    __shared__ __attribute__((aligned(16))) unsigned char bbuf[2 * BELEMS * 2];
 
     // tiles are numbered e * walker_blocks(W) + walker block, so that
     // concurrently resident workgroups share the same AO windows of A; row r
@@ -584,26 +874,19 @@ __device__ __forceinline__ void contract_body(const Job& j, int bx, int by, int 
     constexpr int MSUB = P::MSUB, NSB = P::NSB;
     const int nsub = min(MSUB, (nmo - n0 + NSB - 1) / NSB);  // sub-blocks below nmo (uniform)
     f32x16 acc32[MSUB][5];
-    f64x4 acc64[MSUB][5][2];
 #pragma unroll
-    for (int sb = 0; sb < MSUB; ++sb) {
-        if constexpr (MODE == QSL_FP64) {
-            for (int d = 0; d < 5; ++d)
-                for (int h = 0; h < 2; ++h) acc64[sb][d][h] = f64x4{0, 0, 0, 0};
-        } else {
-            for (int d = 0; d < 5; ++d)
-                for (int r = 0; r < 16; ++r) acc32[sb][d][r] = 0.f;
-        }
-    }
+    for (int sb = 0; sb < MSUB; ++sb)
+        for (int d = 0; d < 5; ++d)
+            for (int r = 0; r < 16; ++r) acc32[sb][d][r] = 0.f;
     bool tie = false;
     // the records of a chunk's windows in LDS (two buffers, by chunk parity):
     // the AO evaluation reads them many times per thread, from LDS rather
     // than through dependent global loads; chunk c + 1 is copied during the
     // products of chunk c
-    // (the f32 modes keep the record prefix they read, RQ pieces of 16 bytes,
-    // back to back; a wave's direct global-to-LDS load fills 64 consecutive
-    // pieces, no registers involved)
-    constexpr int RQ = MODE == QSL_FP64 ? WINREC_Q64 : WINREC_Q32;
+    // (the record prefix that is read, RQ pieces of 16 bytes, back to back; a
+    // wave's direct global-to-LDS load fills 64 consecutive pieces, no
+    // registers involved)
+    constexpr int RQ = WINREC_Q32;
     constexpr int NPASS = (KW * RQ + P::THREADS - 1) / P::THREADS;
     __shared__ __attribute__((aligned(16))) uint4 wrecq[2][NPASS * P::THREADS];
     auto rec = [&](int buf, int wl) -> const WinRec& { return *(const WinRec*)&wrecq[buf][wl * RQ]; };
@@ -640,30 +923,22 @@ __device__ __forceinline__ void contract_body(const Job& j, int bx, int by, int 
                 const double r[3] = {epos[e][0], epos[e][1], epos[e][2]};
                 rec_values<T, SPT>(rec(buf, wl), s.T, js, r, vals, tie);
             }
-            if constexpr (MODE == QSL_BF16X3) {
-                uint16_t* bh = (uint16_t*)bbuf;
-                uint16_t* bl = bh + BELEMS;
+            uint16_t* bh = (uint16_t*)bbuf;
+            uint16_t* bl = bh + BELEMS;
 #pragma unroll
-                for (int d = 0; d < 5; ++d) {
-                    uint32_t hv[SPT / 2], lv[SPT / 2];
+            for (int d = 0; d < 5; ++d) {
+                uint32_t hv[SPT / 2], lv[SPT / 2];
 #pragma unroll
-                    for (int p = 0; p < SPT / 2; ++p) bf16_split2(vals[d][2 * p], vals[d][2 * p + 1], hv[p], lv[p]);
-                    uint16_t* ph = bh + (d * TE + e) * LD + wl * WIN + js;
-                    uint16_t* pl = bl + (d * TE + e) * LD + wl * WIN + js;
-                    if constexpr (SPT == WIN) {
-                        *(uint4*)ph = uint4{hv[0], hv[1], hv[2], hv[3]};
-                        *(uint4*)pl = uint4{lv[0], lv[1], lv[2], lv[3]};
-                    } else {
-                        *(uint2*)ph = uint2{hv[0], hv[1]};
-                        *(uint2*)pl = uint2{lv[0], lv[1]};
-                    }
+                for (int p = 0; p < SPT / 2; ++p) bf16_split2(vals[d][2 * p], vals[d][2 * p + 1], hv[p], lv[p]);
+                uint16_t* ph = bh + (d * TE + e) * LD + wl * WIN + js;
+                uint16_t* pl = bl + (d * TE + e) * LD + wl * WIN + js;
+                if constexpr (SPT == WIN) {
+                    *(uint4*)ph = uint4{hv[0], hv[1], hv[2], hv[3]};
+                    *(uint4*)pl = uint4{lv[0], lv[1], lv[2], lv[3]};
+                } else {
+                    *(uint2*)ph = uint2{hv[0], hv[1]};
+                    *(uint2*)pl = uint2{lv[0], lv[1]};
                 }
-            } else {
-                T* bt = (T*)bbuf;
-#pragma unroll
-                for (int d = 0; d < 5; ++d)
-#pragma unroll
-                    for (int j = 0; j < SPT; ++j) bt[(d * TE + e) * LD + wl * WIN + js + j] = vals[d][j];
             }
         }
         __syncthreads();
@@ -671,7 +946,7 @@ __device__ __forceinline__ void contract_body(const Job& j, int bx, int by, int 
         // ---- phase M: MFMA over the chunk (the next chunk's records load
         // meanwhile; pieces of windows past the list are never read)
         if (c0 + KW < nwin) fetch_recs(buf ^ 1, c0 + KW);
-        if constexpr (MODE == QSL_BF16X3) {
+        {
             const uint16_t* bh = (const uint16_t*)bbuf;
             const uint16_t* bl = bh + BELEMS;
             const int oct = lane >> 5;
@@ -724,24 +999,6 @@ __device__ __forceinline__ void contract_body(const Job& j, int bx, int by, int 
                         acc32[sb][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl[d], bah, acc32[sb][d], 0, 0, 0);
                 }
             }
-        } else {
-            const double* bt = (const double*)bbuf;
-            const int kk = lane >> 4;
-            for (int ks = 0; ks < KC / 4; ++ks) {
-                const int c = ks * 4 + kk;
-                const int slot = wq[c / WIN] * WIN + (c % WIN);
-#pragma unroll
-                for (int sb = 0; sb < MSUB; ++sb) {
-                    if (sb >= nsub) break;
-                    const int mo = n0 + sb * NSB + wave * 16 + (lane & 15);
-                    const double b = AT64[(size_t)slot * ldn + mo];
-                    for (int d = 0; d < 5; ++d)
-                        for (int h = 0; h < 2; ++h) {
-                            const double a = bt[(d * TE + h * 16 + (lane & 15)) * LD + c];
-                            acc64[sb][d][h] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc64[sb][d][h], 0, 0, 0);
-                        }
-                }
-            }
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the next chunk's records are in LDS
         __syncthreads();
@@ -752,61 +1009,51 @@ __device__ __forceinline__ void contract_body(const Job& j, int bx, int by, int 
     // ---- store C[w][d][e][mo]
 #pragma unroll
     for (int sb = 0; sb < MSUB; ++sb) {
-        if constexpr (MODE == QSL_FP64) {
-            double* C = (double*)Cout;
-            const int mo = n0 + sb * NSB + wave * 16 + (lane & 15);
-            if (mo < nmo) {
-                for (int d = 0; d < 5; ++d)
-                    for (int h = 0; h < 2; ++h)
-                        for (int r = 0; r < 4; ++r) {
-                            // v_mfma_f64_16x16x4f64 result: row (lane / 16) + 4 r, column lane % 16
-                            const int el = h * 16 + (lane >> 4) + 4 * r;
-                            if (el < ne) gmem(C)[(((size_t)(w0 + el) * 5 + d) * n + eidx) * nmo + mo] = acc64[sb][d][h][r];
-                        }
-            }
-        } else {
-            float* C = (float*)Cout;
-            const int mo = n0 + sb * NSB + wave * 32 + (lane & 31);
-            if (mo < nmo) {
-                for (int d = 0; d < 5; ++d)
-                    for (int r = 0; r < 16; ++r) {
-                        const int el = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                        if (el < ne) gmem(C)[(((size_t)(w0 + el) * 5 + d) * n + eidx) * nmo + mo] = acc32[sb][d][r];
-                    }
-            }
+        float* C = (float*)Cout;
+        const int mo = n0 + sb * NSB + wave * 32 + (lane & 31);
+        if (mo < nmo) {
+            for (int d = 0; d < 5; ++d)
+                for (int r = 0; r < 16; ++r) {
+                    const int el = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                    if (el < ne) gmem(C)[(((size_t)(w0 + el) * 5 + d) * n + eidx) * nmo + mo] = acc32[sb][d][r];
+                }
         }
     }
-    }  // FP64 / BF16X3
 }
 
-template <int MODE>
-__global__ __launch_bounds__(CT_WAVES * 64, 2) void contract_batched(const Job* jobs, const int* prefix, int njobs) {
-    batch_block(jobs, prefix, njobs,
-                [&](const Job& j, int bx, int by, int) __attribute__((always_inline)) {
-                    contract_body<MODE>(j, bx, by, threadIdx.x);
-                });
+// The workgroup shapes: FP32 tiles 0, 1, 2, split BF16, FP64 with 4 and 8 waves.
+enum { CS_F32 = 0, CS_BF16X3 = 3, CS_F64 = 4, CS_COUNT = 6 };
+template <int SHAPE>
+struct CS {
+    static constexpr int THREADS = SHAPE == CS_F64 + 1 ? F64T<8>::THREADS : CT_WAVES * 64;
+    static constexpr int WPE = SHAPE == CS_F32 + 1 ? F32T<1>::MINB : 2;  // waves per SIMD
+    static constexpr int PER_CU = WPE * 256 / THREADS;                   // workgroups per CU
+    static __device__ __forceinline__ void body(const Job& j, int bx, int by, int tid) {
+        if constexpr (SHAPE == CS_F64 + 1) contract_f64_body<8>(j, bx, by, tid);
+        else if constexpr (SHAPE == CS_F64) contract_f64_body<4>(j, bx, by, tid);
+        else if constexpr (SHAPE == CS_BF16X3) contract_bf16x3_body(j, bx, by, tid);
+        else contract_f32_body<SHAPE>(j, bx, by, tid);
+    }
+};
+static int contract_shape(int mode, int tile) {
+    return mode == QSL_FP64 ? CS_F64 + (tile ? 1 : 0) : mode == QSL_BF16X3 ? CS_BF16X3 : CS_F32 + tile;
 }
 
-__global__ __launch_bounds__(CT_WAVES * 64, F32T<1>::MINB) void contract_batched_f32t1(const Job* jobs,
-                                                                                       const int* prefix, int njobs) {
+template <int SHAPE>
+__global__ __launch_bounds__(CS<SHAPE>::THREADS, CS<SHAPE>::WPE) void contract_batched(const Job* jobs,
+                                                                                      const int* prefix, int njobs) {
     batch_block(jobs, prefix, njobs, [&](const Job& j, int bx, int by, int) __attribute__((always_inline)) {
-        contract_f32_body<1>(j, bx, by, threadIdx.x);
-    });
-}
-
-__global__ __launch_bounds__(CT_WAVES * 64, F32T<2>::MINB) void contract_batched_f32t2(const Job* jobs,
-                                                                                       const int* prefix, int njobs) {
-    batch_block(jobs, prefix, njobs, [&](const Job& j, int bx, int by, int) __attribute__((always_inline)) {
-        contract_f32_body<2>(j, bx, by, threadIdx.x);
+        CS<SHAPE>::body(j, bx, by, threadIdx.x);
     });
 }
 
 // Persistent form: `gridDim.x` resident workgroups take the items of the
 // work list in order from a device counter (zeroed before the launch) until
 // it passes the last; every workgroup leaves once the counter does.
-template <int MODE, int TILE>
-__device__ __forceinline__ void contract_persist_body(const Job* __restrict__ jobs, const int* __restrict__ prefix,
-                                                      int njobs, unsigned* __restrict__ queue) {
+template <int SHAPE>
+__global__ __launch_bounds__(CS<SHAPE>::THREADS, CS<SHAPE>::WPE) void contract_persist(const Job* jobs,
+                                                                                      const int* prefix, int njobs,
+                                                                                      unsigned* queue) {
     __shared__ int s_item;
     const int total = prefix[njobs];
     for (;;) {
@@ -822,34 +1069,19 @@ __device__ __forceinline__ void contract_persist_body(const Job* __restrict__ jo
         const int ji = __builtin_amdgcn_readfirstlane(find_job(prefix, njobs, b));
         const Job& j = jobs[ji];
         const int lb = b - prefix[ji];
-        if constexpr (MODE == QSL_FP32) contract_f32_body<TILE>(j, lb % j.gx, (lb / j.gx) % j.gy, tid);
-        else contract_body<MODE>(j, lb % j.gx, (lb / j.gx) % j.gy, tid);
+        CS<SHAPE>::body(j, lb % j.gx, (lb / j.gx) % j.gy, tid);
     }
 }
 
-template <int MODE>
-__global__ __launch_bounds__(CT_WAVES * 64, 2) void contract_persist(const Job* jobs, const int* prefix, int njobs,
-                                                                     unsigned* queue) {
-    contract_persist_body<MODE, 0>(jobs, prefix, njobs, queue);
-}
-
-__global__ __launch_bounds__(CT_WAVES * 64, F32T<1>::MINB) void contract_persist_f32t1(const Job* jobs,
-                                                                                       const int* prefix, int njobs,
-                                                                                       unsigned* queue) {
-    contract_persist_body<QSL_FP32, 1>(jobs, prefix, njobs, queue);
-}
-
-__global__ __launch_bounds__(CT_WAVES * 64, F32T<2>::MINB) void contract_persist_f32t2(const Job* jobs,
-                                                                                       const int* prefix, int njobs,
-                                                                                       unsigned* queue) {
-    contract_persist_body<QSL_FP32, 2>(jobs, prefix, njobs, queue);
-}
+// Eight waves from 129 MOs on (one evaluation of the AOs for up to 256 MOs:
+// 9.5 ms at 217 MOs, 11.4 with four waves and two evaluations); below, four
+// waves hold every MO and two workgroups per CU overlap.
+int contract_f64_tile(int nmo) { return nmo > F64T<4>::NB ? 1 : 0; }
 
 // Grid of the contraction phase of a Job: tiles x MO blocks.
 void contract_grid(Job& j) {
-    const int nb = j.mode == QSL_FP64 ? CT<QSL_FP64>::NB
-                                      : (j.mode == QSL_FP32 ? (j.f32_tile == 1 ? F32T<1>::NB : F32T<0>::NB)
-                                                            : CT<QSL_BF16X3>::NB);
+    const int nb = j.mode == QSL_FP64 ? (j.f32_tile ? F64T<8>::NB : F64T<4>::NB)
+                                      : (j.mode == QSL_FP32 ? (j.f32_tile == 1 ? F32T<1>::NB : F32T<0>::NB) : CT::NB);
     j.gx = (int)electron_tiles(j.n, j.W);
     j.gy = (j.mo.n + nb - 1) / nb;  // MO blocks (n for a Slater matrix)
     j.gz = 1;
@@ -868,6 +1100,7 @@ __global__ void store_job_kernel(Job j, Job* dst, int* prefix) {
 
 hipError_t launch_contract(const Job& j0, hipStream_t st) {
     Job j = j0;
+    if (j.mode == QSL_FP64) j.f32_tile = contract_f64_tile(j.mo.n);
     contract_grid(j);
     if (!j.n || !j.W) return hipSuccess;
     if (!j.jobslot) return hipErrorInvalidValue;  // every caller's workspace holds one
@@ -877,25 +1110,24 @@ hipError_t launch_contract(const Job& j0, hipStream_t st) {
     return launch_contract_batched(j.mode, j.f32_tile, nullptr, dj, pre, 1, j.gx * j.gy, st);
 }
 
-int contract_per_cu(int mode, int tile) { return mode == QSL_FP32 && tile == 1 ? F32T<1>::MINB : 2; }
+int contract_per_cu(int mode, int tile) {
+    static const int per_cu[CS_COUNT] = {CS<0>::PER_CU, CS<1>::PER_CU, CS<2>::PER_CU,
+                                         CS<3>::PER_CU, CS<4>::PER_CU, CS<5>::PER_CU};
+    return per_cu[contract_shape(mode, tile)];
+}
 
 hipError_t launch_contract_batched(int mode, int tile, unsigned* queue, const Job* jobs, const int* prefix, int njobs,
                                    int grid, hipStream_t st) {
-    constexpr int T = CT_WAVES * 64;
     if (grid <= 0) return hipSuccess;
-    const bool t1 = mode == QSL_FP32 && tile == 1, t2 = mode == QSL_FP32 && tile == 2;
-    if (queue) {
-        if (mode == QSL_FP64) contract_persist<QSL_FP64><<<grid, T, 0, st>>>(jobs, prefix, njobs, queue);
-        else if (t1) contract_persist_f32t1<<<grid, T, 0, st>>>(jobs, prefix, njobs, queue);
-        else if (t2) contract_persist_f32t2<<<grid, T, 0, st>>>(jobs, prefix, njobs, queue);
-        else if (mode == QSL_FP32) contract_persist<QSL_FP32><<<grid, T, 0, st>>>(jobs, prefix, njobs, queue);
-        else contract_persist<QSL_BF16X3><<<grid, T, 0, st>>>(jobs, prefix, njobs, queue);
-    } else {
-        if (mode == QSL_FP64) contract_batched<QSL_FP64><<<grid, T, 0, st>>>(jobs, prefix, njobs);
-        else if (t1) contract_batched_f32t1<<<grid, T, 0, st>>>(jobs, prefix, njobs);
-        else if (t2) contract_batched_f32t2<<<grid, T, 0, st>>>(jobs, prefix, njobs);
-        else if (mode == QSL_FP32) contract_batched<QSL_FP32><<<grid, T, 0, st>>>(jobs, prefix, njobs);
-        else contract_batched<QSL_BF16X3><<<grid, T, 0, st>>>(jobs, prefix, njobs);
+    switch (contract_shape(mode, tile)) {
+#define QSL_CT(S)                                                                                            \
+    case S:                                                                                                  \
+        if (queue) contract_persist<S><<<grid, CS<S>::THREADS, 0, st>>>(jobs, prefix, njobs, queue);         \
+        else contract_batched<S><<<grid, CS<S>::THREADS, 0, st>>>(jobs, prefix, njobs);                      \
+        break;
+        QSL_CT(0) QSL_CT(1) QSL_CT(2) QSL_CT(3) QSL_CT(4) QSL_CT(5)
+#undef QSL_CT
+        default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

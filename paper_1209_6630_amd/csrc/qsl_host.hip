@@ -467,6 +467,24 @@ qsl_status qsl_system_create(const qsl_system_desc* d, qsl_system** out) {
             }
         }
 
+        std::vector<SlotRec64> slot_rec64(std::max(n_slots, 1));
+        for (int q = 0; q < n_slots; ++q) {
+            SlotRec64& r = slot_rec64[q];
+            memset(&r, 0, sizeof r);
+            const int sh = slot_shell[q];
+            r.pw = -1;
+            const int at = win_atom[q / WIN];
+            for (int k = 0; k < 3; ++k) r.pos[k] = d->atom_xyz[3 * at + k];
+            if (sh < 0) continue;
+            r.pw = slot_pow[q] & 0xffff;
+            r.f64 = slot_f[q];
+            r.np = sh_np[sh];
+            for (int k = 0; k < sh_np[sh]; ++k) {
+                r.ex[k] = ex[p0[sh] + k];
+                r.c64[k] = c64[p0[sh] + k];
+            }
+        }
+
         // device tables in one allocation
         Arena ar;
         size_t o_xyz = ar.add(d->atom_xyz, sizeof(double) * 3 * d->n_atoms);
@@ -486,6 +504,7 @@ qsl_status qsl_system_create(const qsl_system_desc* d, qsl_system** out) {
         size_t o_wgm = ar.add(win_gmin.data(), sizeof(double) * win_gmin.size());
         size_t o_wrec = ar.add(win_rec.data(), sizeof(WinRec) * win_rec.size());
         size_t o_srec = ar.add(slot_rec.data(), sizeof(SlotRec) * slot_rec.size());
+        size_t o_srec64 = ar.add(slot_rec64.data(), sizeof(SlotRec64) * slot_rec64.size());
         // MO copies per spin
         size_t o_mo[2][10];
         int ldn[2];
@@ -534,6 +553,7 @@ qsl_status qsl_system_create(const qsl_system_desc* d, qsl_system** out) {
         D.win_atom = (const int*)(b + o_wat); D.win_gmin = (const double*)(b + o_wgm);
         D.win_rec = (const WinRec*)(b + o_wrec);
         D.slot_rec = (const SlotRec*)(b + o_srec);
+        D.slot_rec64 = (const SlotRec64*)(b + o_srec64);
         for (int sp = 0; sp < 2; ++sp) {
             DevMO& m = S->mo[sp];
             m.n = sp ? d->n_dn : d->n_up;

@@ -71,6 +71,18 @@ struct SlotRec {
 };
 static_assert(sizeof(SlotRec) % 16 == 0, "slot records are loaded in 16-byte pieces");
 
+// The same for the FP64 contraction.
+struct SlotRec64 {
+    double pos[3];
+    double f64;
+    double ex[QSL_PMAX];
+    double c64[QSL_PMAX];
+    int pw;
+    int np;
+    int pad[2];
+};
+static_assert(sizeof(SlotRec64) % 16 == 0, "slot records are loaded in 16-byte pieces");
+
 // Device view of a system, passed to kernels by value.
 struct DevSys {
     int n_atoms, n_shells, n_slots, n_win, n_basis;
@@ -94,6 +106,7 @@ struct DevSys {
     const int* win_atom;      // [n_win]
     const double* win_gmin;   // [n_win] min exponent over shells meeting the window
     const SlotRec* slot_rec;  // [n_slots]
+    const SlotRec64* slot_rec64;  // [n_slots]
 };
 
 // MO coefficient copies of one spin, padded: n rows -> ldn (multiple of 128).
@@ -329,7 +342,8 @@ struct Job {
     double* gjws;            // blocked inversion (gj_blocked(n)): W x gj_ws_doubles(n)
     uint16_t* gsplit;        // BF16X3 adjoint: W x gsplit_elems(n) hi, then as many lo
     void* jobslot;           // per-system launches: device copy of the Job and its block prefix
-    int f32_tile;            // FP32 products: 0 = 256 MOs per workgroup, 1 = 128, 2 = 256 on split bf16
+    int f32_tile;            // FP32 products: 0 = 256 MOs per workgroup, 1 = 128, 2 = 256 on split bf16;
+                             // FP64 products: 0 = up to 128 MOs per workgroup, 1 = up to 256
     // Deterministic dA: one launch per electron range t_fix (-1: one launch
     // for all ranges, atomic flush), each walker group adding its block into
     // its own partial sum dApart[wb][n][N_b] (float, or double in FP64) with
@@ -502,10 +516,13 @@ hipError_t launch_group_slots_batched(const Job* jobs, const int* prefix, int nj
 hipError_t launch_screen(const Job& j, int group, hipStream_t st);
 hipError_t launch_screen_batched(const Job* jobs, const int* prefix, int njobs, int grid, int group,
                                     hipStream_t st);
-// Fused AO evaluation + the five AO->MO products C_n = A B_n.
+// Fused AO evaluation + the five AO->MO products C_n = A B_n.  The workgroup
+// shape of a launch is its Jobs' f32_tile; the FP64 one follows from the
+// largest MO count of the launch.
+int contract_f64_tile(int nmo);
 void contract_grid(Job& j);
 hipError_t launch_contract(const Job& j, hipStream_t st);
-// tile: the FP32 workgroup shape (Job.f32_tile); queue: NULL for one
+// tile: the workgroup shape (Job.f32_tile); queue: NULL for one
 // workgroup per item, else a zeroed device counter that `grid` resident
 // workgroups draw items from (persistent launch).
 hipError_t launch_contract_batched(int mode, int tile, unsigned* queue, const Job* jobs, const int* prefix, int njobs,

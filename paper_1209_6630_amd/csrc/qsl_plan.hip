@@ -171,6 +171,12 @@ static qsl_status prepare(qsl_plan* p, hipStream_t st) {
                 p->bjobs.push_back(b);
             }
         }
+    // FP64 products: one workgroup shape for the launch, by the largest system
+    if (p->mode == QSL_FP64) {
+        int nmo = 0;
+        for (const Job& f : p->fjobs) nmo = std::max(nmo, f.W ? f.mo.n : 0);
+        for (Job& f : p->fjobs) f.f32_tile = contract_f64_tile(nmo);
+    }
     for (auto& L : p->ph) { L.jobs.clear(); L.prefix.clear(); }
     p->da_t.clear();
     for (const Job& f : p->fjobs) {
@@ -367,7 +373,7 @@ static qsl_status enqueue(qsl_plan* p, hipStream_t st) {
         auto& C = p->ph[PH_CONTRACT];
         if (C.blocks()) {
             ProfScope ps(contract_name(mode), st);
-            const int tile = p->tune.contract_tile;
+            const int tile = C.jobs[0].f32_tile;
             unsigned* queue = nullptr;
             int grid = C.blocks();
             if (p->tune.persistent) {
