@@ -39,18 +39,22 @@ static void powers(int l, int c, int p[3]) {
     for (int k = 0; k < 3; ++k) p[k] = l == 0 ? 0 : (l == 1 ? P1[c][k] : P2[c][k]);
 }
 
-// Byte arena: host staging of all device tables, copied in one transfer.
+// Byte arena of a system's device tables: contents first (add), copied in one
+// transfer, then regions that only start at zero (reserve).  These, the copies
+// of the orbital coefficients in every layout, never exist on the host: at
+// 1731 electrons they are 35 MB of a creation's 18 ms, 9 ms without.
 struct Arena {
     std::vector<char> buf;
+    size_t total = 0;
     size_t add(const void* src, size_t bytes) {
-        size_t off = (buf.size() + 255) & ~size_t(255);
-        buf.resize(off + std::max<size_t>(bytes, 1));
+        const size_t off = reserve(bytes);
+        buf.resize(total);
         if (bytes) memcpy(buf.data() + off, src, bytes);
         return off;
     }
     size_t reserve(size_t bytes) {
-        size_t off = (buf.size() + 255) & ~size_t(255);
-        buf.resize(off + std::max<size_t>(bytes, 1));
+        const size_t off = (total + 255) & ~size_t(255);
+        total = off + std::max<size_t>(bytes, 1);
         return off;
     }
 };
@@ -521,13 +525,15 @@ qsl_status qsl_system_create(const qsl_system_desc* d, qsl_system** out) {
             o_mo[sp][9] = ar.reserve(cells * 8);
         }
         void* blk = nullptr;
-        hipError_t e = hipMalloc(&blk, ar.buf.size());
+        hipError_t e = hipMalloc(&blk, ar.total);
         if (e != hipSuccess) {
             delete S;
             set_error(std::string("hipMalloc of system tables: ") + hipGetErrorString(e));
             return e == hipErrorOutOfMemory ? QSL_ERR_OOM : QSL_ERR_HIP;
         }
         e = hipMemcpy(blk, ar.buf.data(), ar.buf.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemset((char*)blk + ar.buf.size(), 0, ar.total - ar.buf.size());
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
         if (e != hipSuccess) { hipFree(blk); delete S; return hip_fail(e, "upload of system tables"); }
         S->dev_block = blk;
         char* b = (char*)blk;
