@@ -57,7 +57,7 @@ struct GJT {
     static constexpr int WPE = NT <= 4 ? 4 : NT <= 9 ? 3 : 2;  // waves per SIMD
     static constexpr int NP = 16 * NT;
     static constexpr int RPL = (NP + 63) / 64;      // panel rows per lane
-    static constexpr bool EXACT = NT <= 8;          // pivot by the full |a| (else to 2^-12)
+    static constexpr bool EXACT = NT <= GJ_V_APPROX;  // pivot by the full |a| (else to 2^-12)
     // row strides in doubles: 8 mod 16, so that four rows of 16 consecutive
     // values cover every LDS bank evenly (and 8 spare entries)
     static constexpr int LS = NP + 8;
@@ -457,7 +457,8 @@ __device__ __forceinline__ void gjt_panels(const GJArgs& j, GJShared<NT>& S, int
 // that the last panel has 16 columns; its inverse and determinant add
 // nothing).  A whole column tile's loads are in flight at once.  A row is
 // read past its end (into the next row, or the gradient block after C_1)
-// rather than clamped, except where the matrix is too small for that.
+// rather than clamped, except where the matrix is too small for that (NT <= 2
+// also serves n < 8; a larger NT has n >= 8, and 4 n n + n >= 16 * 14).
 template <int NT, typename Tin>
 __device__ __forceinline__ void gjt_load(const Tin* __restrict__ C1, int n, int u, int lane,
                                          f64x4 (&acc)[NT][GJT<NT>::CT]) {
@@ -721,6 +722,11 @@ int gj_variant(int n) { return gj_blocked(n) ? GJ_V_BLOCKED : (std::max(n, 1) - 
 int gj_job_variant(const Job& j) {
     const int v = gj_variant(j.n);
     return v == GJ_V_BLOCKED ? v : std::min(GJ_V_BLOCKED - 1, v + std::max(0, j.gj_bias));
+}
+
+void gj_share_variant(int (&v)[2], const int (&n)[2]) {
+    const auto kind = [](int x) { return x == GJ_V_BLOCKED ? 2 : x >= GJ_V_APPROX ? 1 : 0; };
+    if (v[0] >= 0 && v[1] >= 0 && kind(v[0]) == kind(v[1]) && std::min(n[0], n[1]) >= 8) v[0] = v[1] = std::max(v[0], v[1]);
 }
 
 static hipError_t gj_dispatch(const GJArgs& a, int v, const Job* jobs, const int* prefix, int njobs, int grid,

@@ -153,6 +153,8 @@ WsLayout ws_layout(const DevSys& d, int64_t W, int gw, int mode, bool by_e) {
         L.gj_off[s] = off;
         if (gj_blocked((int)n)) off = round_up(off + (size_t)W * gj_ws_doubles((int)n) * sizeof(double), 256);
     }
+    L.call_off = off;
+    off += CALL_LISTS_BYTES;
     L.fwd_total = std::max<size_t>(off, 256);
     for (int s = 0; s < 2; ++s) {
         int n = n_spin(d, s);
@@ -741,38 +743,108 @@ static qsl_status forward_check(qsl_system* sys, const qsl_fwd_args* a) {
     return QSL_OK;
 }
 
+// One block per phase: the taking-part spins' Jobs with their grids, and the
+// block prefix.
+__global__ void store_lists_kernel(Job a, Job b, CallGrids g, char* base) {
+    const int ph = blockIdx.x;
+    Job* dst = (Job*)(base + ph * CALL_LIST_BYTES);
+    int* prefix = (int*)(base + ph * CALL_LIST_BYTES + 2 * sizeof(Job));
+    const int(&ga)[3] = g.g[ph][0];
+    const int(&gb)[3] = g.g[ph][1];
+    const int na = ga[0] * ga[1] * ga[2], nb = gb[0] * gb[1] * gb[2];
+    if (threadIdx.x == 0 && ga[0]) {
+        *dst = a;
+        dst->gx = ga[0]; dst->gy = ga[1]; dst->gz = ga[2];
+    }
+    if (threadIdx.x == 64 && gb[0]) {
+        if (ga[0]) ++dst;
+        *dst = b;
+        dst->gx = gb[0]; dst->gy = gb[1]; dst->gz = gb[2];
+    }
+    if (threadIdx.x == 128) {
+        prefix[0] = 0;
+        prefix[1] = ga[0] ? na : nb;
+        prefix[2] = na + nb;
+        prefix[3] = 0;  // spin 1 by itself
+        prefix[4] = nb;
+    }
+}
+
+hipError_t CallLists::store(hipStream_t st) const {
+    store_lists_kernel<<<CALL_PHASES, 192, 0, st>>>(job[0], job[1], grids, base);
+    return hipGetLastError();
+}
+
+static const char* contract_label(int mode) {
+    return mode == QSL_FP64 ? "contract_fp64" : mode == QSL_FP32 ? "contract_fp32" : "contract_bf16x3";
+}
+
 // The forward's launches on workspace ws (at least the forward's part of
-// ws_layout); enqueues kernels only.
+// ws_layout); enqueues kernels only.  Both spins share one launch per phase:
+// a small population leaves most of the chip idle, and two launches in a row
+// take twice one's latency (two spins of 22 electrons, 64 walkers: 138 us one
+// spin after the other).
 static qsl_status forward_enqueue(qsl_system* sys, const qsl_fwd_args* a, char* ws, hipStream_t st) {
+    enum { SORT, SCREEN, CONTRACT, GJ0, GJ1, EPILOGUE };
     const WsLayout L = ws_layout(sys->d, a->W, 1, a->mode, false);  // the forward's part only
     hipError_t e;
     if (a->status && (e = fill_u32(a->status, 0u, a->W, st)) != hipSuccess) return hip_fail(e, "status clear");
+    CallLists P(ws + L.call_off);
+    const int nmax = std::max(sys->d.n_up, sys->d.n_dn);
+    int variant[2] = {-1, -1};
     for (int s = 0; s < 2; ++s) {
         // FP32: each electron index's walkers in space-filling-curve order,
         // so the tiles' survivor unions are tighter
         Job j = fwd_job(sys, a, L, ws, s, /*sorted=*/true);
-        if (j.n) {
-            if (j.wperm) {
-                ProfScope ps("walker_order", st);
-                if ((e = launch_wsort(j, st)) != hipSuccess) return hip_fail(e, "walker order kernel");
-            }
-            {
-                ProfScope ps("screen", st);
-                if ((e = launch_screen(j, 0, st)) != hipSuccess) return hip_fail(e, "screen kernel");
-            }
-            {
-                ProfScope ps(a->mode == QSL_FP64 ? "contract_fp64" : a->mode == QSL_FP32 ? "contract_fp32" : "contract_bf16x3", st);
-                if ((e = launch_contract(j, st)) != hipSuccess) return hip_fail(e, "contraction kernel");
-            }
-        }
-        {
-            ProfScope ps("gauss_jordan", st);
-            if ((e = launch_gj(j, st)) != hipSuccess) return hip_fail(e, "inversion kernel");
-        }
-        if (j.n && (a->drift || a->lap)) {
-            ProfScope ps("drift_lap", st);
-            if ((e = launch_epilogue(j, st)) != hipSuccess) return hip_fail(e, "epilogue kernel");
-        }
+        if (!j.n) continue;
+        if (j.mode == QSL_FP64) j.f32_tile = contract_f64_tile(nmax);
+        P.job[s] = j;
+        if (j.wperm) P.add(SORT, s, wsort_blocks(j));
+        P.add(SCREEN, s, screen_blocks(j, 0));
+        contract_grid(j);
+        P.add(CONTRACT, s, j.gx, j.gy, j.gz);
+        variant[s] = gj_job_variant(j);
+        if (a->drift || a->lap) P.add(EPILOGUE, s, epilogue_blocks(j));
+    }
+    gj_share_variant(variant, {sys->d.n_up, sys->d.n_dn});
+    for (int s = 0; s < 2; ++s)
+        if (variant[s] >= 0) P.add(GJ0 + gj_list(variant, s), s, a->W);
+    if ((e = P.store(st)) != hipSuccess) return hip_fail(e, "job lists");
+    if (P.any(SORT)) {
+        ProfScope ps("walker_order", st);
+        e = P.run(SORT, [&](const Job* js, const int* pre, int nj, int nb) { return launch_wsort_batched(js, pre, nj, nb, st); });
+        if (e != hipSuccess) return hip_fail(e, "walker order kernel");
+    }
+    if (P.any(SCREEN)) {
+        ProfScope ps("screen", st);
+        e = P.run(SCREEN, [&](const Job* js, const int* pre, int nj, int nb) { return launch_screen_batched(js, pre, nj, nb, 0, st); });
+        if (e != hipSuccess) return hip_fail(e, "screen kernel");
+    }
+    if (P.any(CONTRACT)) {
+        ProfScope ps(contract_label(a->mode), st);
+        const int tile = P.job[sys->d.n_up ? 0 : 1].f32_tile;
+        e = P.run(CONTRACT, [&](const Job* js, const int* pre, int nj, int nb) {
+            return launch_contract_batched(a->mode, tile, nullptr, js, pre, nj, nb, st);
+        });
+        if (e != hipSuccess) return hip_fail(e, "contraction kernel");
+    }
+    for (int ph = GJ0; ph <= GJ1; ++ph) {
+        if (!P.any(ph)) continue;
+        ProfScope ps("gauss_jordan", st);
+        const int v = ph == GJ1 || variant[0] < 0 ? variant[1] : variant[0];
+        e = P.run(ph, [&](const Job* js, const int* pre, int nj, int nb) {
+            return v == GJ_V_BLOCKED ? launch_gjb_batched(a->mode, js, pre, nj, nb, nmax, st)
+                                     : launch_gj_batched(v, js, pre, nj, nb, st);
+        });
+        if (e != hipSuccess) return hip_fail(e, "inversion kernel");
+    }
+    for (int s = 0; s < 2; ++s)  // a spin without electrons: log|det| = 0, sign = +1
+        if (!n_spin(sys->d, s) && (e = launch_gj(fwd_job(sys, a, L, ws, s), st)) != hipSuccess)
+            return hip_fail(e, "empty spin kernel");
+    if (P.any(EPILOGUE)) {
+        ProfScope ps("drift_lap", st);
+        e = P.run(EPILOGUE, [&](const Job* js, const int* pre, int nj, int nb) { return launch_epilogue_batched(a->mode, js, pre, nj, nb, st); });
+        if (e != hipSuccess) return hip_fail(e, "epilogue kernel");
     }
     return QSL_OK;
 }
@@ -781,7 +853,8 @@ static qsl_status forward_enqueue(qsl_system* sys, const qsl_fwd_args* a, char* 
 // GPU, held until the process ends.  Host code never passes `scratch` itself
 // to a kernel (on the host it is only a stand-in for the symbol): the device
 // address of each GPU's copy comes from hipGetSymbolAddress, once per device.
-static __device__ __align__(256) unsigned char scratch[QSL_NOALLOC_SCRATCH_BYTES];
+// (The call's job lists come on top of the documented bytes.)
+static __device__ __align__(256) unsigned char scratch[QSL_NOALLOC_SCRATCH_BYTES + CALL_LISTS_BYTES];
 constexpr int SCRATCH_MAX_DEVICES = 64;
 static void* g_scratch_ptr[SCRATCH_MAX_DEVICES] = {};
 static std::mutex g_scratch_mu;
@@ -818,7 +891,7 @@ qsl_status qsl_forward_noalloc(qsl_system* sys, const qsl_fwd_args* a, void* str
     qsl_status r = forward_check(sys, a);
     if (r != QSL_OK || a->W == 0) return r;
     const WsLayout L = ws_layout(sys->d, a->W, 1, a->mode, false);
-    if (L.fwd_total > (size_t)QSL_NOALLOC_SCRATCH_BYTES)
+    if (L.fwd_total > (size_t)QSL_NOALLOC_SCRATCH_BYTES + CALL_LISTS_BYTES)
         return bad(QSL_ERR_WORKSPACE, "noalloc: the forward of this many walkers needs " + std::to_string(L.fwd_total) +
                                           " bytes of workspace, more than the " +
                                           std::to_string((size_t)QSL_NOALLOC_SCRATCH_BYTES) + " of the static scratch");
@@ -862,59 +935,83 @@ qsl_status qsl_backward(qsl_system* sys, const qsl_bwd_args* a, void* stream) {
     // with the drift, dR is written whole (every electron of both spins)
     if (a->dR && !a->drift && (e = fill_f64(a->dR, 0.0, a->W * N * 3, st)) != hipSuccess)
         return hip_fail(e, "dR clear");
+    // both spins in one launch per phase, as the forward
+    enum { SORT, SCREEN, DR, ADJ_H, GROUP, G, DA };
+    CallLists P(ws + L.call_off);
     for (int s = 0; s < 2; ++s) {
         Job j = bwd_job(sys, a, L, ws, s, gw, by_e);
         if (!j.n) continue;
-        if (j.wperm) {  // the walker order of the tiles (as the forward's)
-            ProfScope ps("walker_order", st);
-            if ((e = launch_wsort(j, st)) != hipSuccess) return hip_fail(e, "walker order kernel");
-        }
-        const bool f32acc = j.dA32 != nullptr;
-        if (f32acc && (e = fill_u32((uint32_t*)j.dA32, 0u, (int64_t)j.n * d.n_basis, st)) != hipSuccess)
+        P.job[s] = j;
+        if (j.dA32 && (e = fill_u32((uint32_t*)j.dA32, 0u, (int64_t)j.n * d.n_basis, st)) != hipSuccess)
             return hip_fail(e, "dA accumulator clear");
+        if (j.wperm) P.add(SORT, s, wsort_blocks(j));  // the walker order of the tiles (as the forward's)
+        const bool dA = a->dA[s] != nullptr;
+        if ((a->dR && !a->drift) || (dA && by_e)) P.add(SCREEN, s, screen_blocks(j, 0));  // the tile lists
         if (a->dR && a->drift) {
-            ProfScope ps("dR_drift", st);
-            if ((e = launch_dr_drift(j, st)) != hipSuccess) return hip_fail(e, "dR kernel");
+            P.add(DR, s, dr_drift_blocks(j));
         } else if (a->dR) {
-            {
-                ProfScope ps("screen", st);
-                if ((e = launch_screen(j, 0, st)) != hipSuccess) return hip_fail(e, "screen kernel");
-            }
-            ProfScope ps("adjoint_h", st);
-            if ((e = launch_adj_h(j, st)) != hipSuccess) return hip_fail(e, "adjoint H kernel");
+            Job h = j;
+            adj_h_grid(h);
+            P.add(ADJ_H, s, h.gx, h.gy, h.gz);
         }
-        if (a->dA[s] && by_e) {
-            // the tile lists (as the forward screens them), then the slot
-            // lists of the (electron, walker group) pairs
-            if (!(a->dR && !a->drift)) {
-                ProfScope ps("screen", st);
-                if ((e = launch_screen(j, 0, st)) != hipSuccess) return hip_fail(e, "screen kernel");
-            }
-            {
-                ProfScope ps("screen_group", st);
-                if ((e = launch_group_slots(j, st)) != hipSuccess) return hip_fail(e, "group slot kernel");
-            }
-            {
-                ProfScope ps("g32", st);
-                if ((e = launch_g32(j, st)) != hipSuccess) return hip_fail(e, "G kernel");
-            }
-            ProfScope ps("adjoint_dA", st);
-            if ((e = launch_adj_dae(j, st)) != hipSuccess) return hip_fail(e, "adjoint dA kernel");
-        } else if (a->dA[s]) {
-            {
-                ProfScope ps("screen_group", st);
-                if ((e = launch_screen(j, 1, st)) != hipSuccess) return hip_fail(e, "group screen kernel");
-            }
-            if (j.gsplit) {
-                ProfScope ps("g_split", st);
-                if ((e = launch_gsplit(j, st)) != hipSuccess) return hip_fail(e, "G split kernel");
-            }
-            ProfScope ps("adjoint_dA", st);
-            if ((e = launch_adj_da(j, st)) != hipSuccess) return hip_fail(e, "adjoint dA kernel");
-        }
-        if (f32acc && (e = launch_finalize_dA(j.dA32, a->dA[s], (int64_t)j.n * d.n_basis, a->accumulate_dA, st)) != hipSuccess)
-            return hip_fail(e, "dA finalize");
+        if (!dA) continue;
+        // the slot lists of the (electron, walker group) pairs, or the window
+        // lists of the groups
+        P.add(GROUP, s, by_e ? group_slots_blocks(j) : screen_blocks(j, 1));
+        if (by_e) P.add(G, s, g32_blocks(j));
+        else if (j.gsplit) P.add(G, s, gsplit_blocks(j));
+        Job t = j;
+        if (by_e) adj_dae_grid(t);
+        else adj_da_grid(t);
+        P.add(DA, s, t.gx, t.gy, t.gz);
     }
+    if ((e = P.store(st)) != hipSuccess) return hip_fail(e, "job lists");
+    if (P.any(SORT)) {
+        ProfScope ps("walker_order", st);
+        e = P.run(SORT, [&](const Job* js, const int* pre, int nj, int nb) { return launch_wsort_batched(js, pre, nj, nb, st); });
+        if (e != hipSuccess) return hip_fail(e, "walker order kernel");
+    }
+    if (P.any(DR)) {
+        ProfScope ps("dR_drift", st);
+        e = P.run(DR, [&](const Job* js, const int* pre, int nj, int nb) { return launch_dr_drift_batched(js, pre, nj, nb, st); });
+        if (e != hipSuccess) return hip_fail(e, "dR kernel");
+    }
+    if (P.any(SCREEN)) {
+        ProfScope ps("screen", st);
+        e = P.run(SCREEN, [&](const Job* js, const int* pre, int nj, int nb) { return launch_screen_batched(js, pre, nj, nb, 0, st); });
+        if (e != hipSuccess) return hip_fail(e, "screen kernel");
+    }
+    if (P.any(ADJ_H)) {
+        ProfScope ps("adjoint_h", st);
+        e = P.run(ADJ_H, [&](const Job* js, const int* pre, int nj, int nb) { return launch_adj_h_batched(a->mode, js, pre, nj, nb, st); });
+        if (e != hipSuccess) return hip_fail(e, "adjoint H kernel");
+    }
+    if (P.any(GROUP)) {
+        ProfScope ps("screen_group", st);
+        e = P.run(GROUP, [&](const Job* js, const int* pre, int nj, int nb) {
+            return by_e ? launch_group_slots_batched(js, pre, nj, nb, st) : launch_screen_batched(js, pre, nj, nb, 1, st);
+        });
+        if (e != hipSuccess) return hip_fail(e, by_e ? "group slot kernel" : "group screen kernel");
+    }
+    if (P.any(G)) {
+        ProfScope ps(by_e ? "g32" : "g_split", st);
+        e = P.run(G, [&](const Job* js, const int* pre, int nj, int nb) {
+            return by_e ? launch_g32_batched(js, pre, nj, nb, st) : launch_gsplit_batched(js, pre, nj, nb, st);
+        });
+        if (e != hipSuccess) return hip_fail(e, by_e ? "G kernel" : "G split kernel");
+    }
+    if (P.any(DA)) {
+        ProfScope ps("adjoint_dA", st);
+        e = P.run(DA, [&](const Job* js, const int* pre, int nj, int nb) {
+            return by_e ? launch_adj_dae_batched(F32_TILE_DEFAULT, js, pre, nj, nb, st)
+                        : launch_adj_da_batched(a->mode, js, pre, nj, nb, st);
+        });
+        if (e != hipSuccess) return hip_fail(e, "adjoint dA kernel");
+    }
+    for (int s = 0; s < 2; ++s)
+        if (P.job[s].dA32 && (e = launch_finalize_dA(P.job[s].dA32, a->dA[s], (int64_t)P.job[s].n * d.n_basis,
+                                                     a->accumulate_dA, st)) != hipSuccess)
+            return hip_fail(e, "dA finalize");
     return QSL_OK;
 }
 

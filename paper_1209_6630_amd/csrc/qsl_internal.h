@@ -467,8 +467,46 @@ __host__ __device__ inline int64_t gsplit_elems(int n) {
     return (int64_t)((n + TE - 1) / TE) * ((n + ADJ_MB - 1) / ADJ_MB * ADJ_MB) * TE;
 }
 
+// Job lists of a call on one system: both spins in one launch per phase.
+constexpr int CALL_PHASES = 8;
+constexpr size_t CALL_LIST_BYTES = (2 * sizeof(Job) + 5 * sizeof(int) + 255) / 256 * 256;
+constexpr size_t CALL_LISTS_BYTES = CALL_PHASES * CALL_LIST_BYTES;
+struct CallGrids {
+    int g[CALL_PHASES][2][3];  // per phase and spin: the Job's grid (x 0: the spin takes no part)
+};
+struct CallLists {
+    explicit CallLists(char* at) : base(at) {}
+    Job job[2]{};
+    CallGrids grids{};
+    char* base;
+    void add(int phase, int spin, int64_t gx, int gy = 1, int gz = 1) {
+        grids.g[phase][spin][0] = (int)gx;
+        grids.g[phase][spin][1] = gy;
+        grids.g[phase][spin][2] = gz;
+    }
+    int64_t blocks(int phase, int spin) const {
+        return (int64_t)grids.g[phase][spin][0] * grids.g[phase][spin][1] * grids.g[phase][spin][2];
+    }
+    bool any(int phase) const { return blocks(phase, 0) + blocks(phase, 1) > 0; }
+    // f(jobs, prefix, number of jobs, blocks): once for both spins, or once
+    // per spin where the two together have more threads (of up to 512 a
+    // block) than a launch can
+    template <typename F>
+    hipError_t run(int phase, F f) const {
+        const Job* js = (const Job*)(base + phase * CALL_LIST_BYTES);
+        const int* pre = (const int*)(js + 2);
+        const int64_t na = blocks(phase, 0), nb = blocks(phase, 1);
+        if (!na || !nb) return na + nb ? f(js, pre, 1, (int)(na + nb)) : hipSuccess;
+        if (na + nb < (1ll << 32) / 512) return f(js, pre, 2, (int)(na + nb));
+        const hipError_t e = f(js, pre, 1, (int)na);
+        return e != hipSuccess ? e : f(js + 1, pre + 3, 1, (int)nb);
+    }
+    hipError_t store(hipStream_t st) const;  // to the device, by one small kernel
+};
+
 struct WsLayout {
     size_t job_off;  // the device Job copy of per-system launches
+    size_t call_off; // the CallLists of a forward or adjoint call
     size_t nwin_off[2], win_off[2], dA32_off[2], gnwin_off[2], gwin_off[2], gj_off[2], gs_off[2], g32_off[2];
     size_t perm_off[2];  // walker order per electron (FP32), [n][W] int
     size_t fwd_total;  // end of the forward's regions (tile lists, blocked-inversion copy)
@@ -532,8 +570,17 @@ int contract_per_cu(int mode, int tile);
 // Gauss-Jordan inversion, log|det| and sign (one block per matrix; the
 // block shape depends on n, so a batched launch serves one variant).
 constexpr int GJ_V_BLOCKED = 14;   // the variants below it are register-resident, n <= 16 (v + 1)
+constexpr int GJ_V_APPROX = 8;     // from this variant on pivots are compared to 2^-12
 int gj_variant(int n);
 int gj_job_variant(const Job& j);  // gj_variant(n) + gj_bias, clamped
+// The variants v of two spins of n electrons (-1: none) raised to a common one
+// where one launch may serve both: both blocked, or both register-resident
+// with the same comparison of pivots (a larger variant than n needs gives the
+// same bits).  Matrices under 8 keep their own: a larger variant reads up to
+// 224 values past the last row of C_1, which from n = 8 on lies in the
+// walker's other derivatives.  And the launch, 0 or 1, a spin then belongs to.
+void gj_share_variant(int (&v)[2], const int (&n)[2]);
+inline int gj_list(const int (&v)[2], int spin) { return spin == 1 && v[0] >= 0 && v[0] != v[1] ? 1 : 0; }
 // Blocked inversion (GJ_V_BLOCKED, 224 < n <= 1024): the launch sequence of one
 // Job, or of the Jobs of a plan (prefix counts matrices, nmax = largest n).
 hipError_t launch_gjb(const Job& j, hipStream_t st);
