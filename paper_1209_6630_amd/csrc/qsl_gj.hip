@@ -124,10 +124,11 @@ struct GJArgs {
     double* logdet;
     int8_t* sign;
     uint32_t* status;
+    int64_t c1_stride;  // values between walkers' C_1
     int n, spin, mode;
 };
 __host__ __device__ __forceinline__ GJArgs gj_args(const Job& j) {
-    return GJArgs{j.C, j.Dinv, j.logdet, j.sign, j.status, j.n, j.spin, j.mode};
+    return GJArgs{j.C, j.Dinv, j.logdet, j.sign, j.status, c1_stride(j), j.n, j.spin, j.mode};
 }
 
 // Search keys of an entry x of row i.  EXACT: the high word of |x| above a
@@ -458,7 +459,7 @@ __device__ __forceinline__ void gjt_panels(const GJArgs& j, GJShared<NT>& S, int
 // nothing).  A whole column tile's loads are in flight at once.  A row is
 // read past its end (into the next row, or the gradient block after C_1)
 // rather than clamped, except where the matrix is too small for that (NT <= 2
-// also serves n < 8; a larger NT has n >= 8, and 4 n n + n >= 16 * 14).
+// also serves n < 8; a larger NT has n >= 8, and 4 n n + n >= GJ_READ_PAST).
 template <int NT, typename Tin>
 __device__ __forceinline__ void gjt_load(const Tin* __restrict__ C1, int n, int u, int lane,
                                          f64x4 (&acc)[NT][GJT<NT>::CT]) {
@@ -508,8 +509,8 @@ __device__ __forceinline__ void gjt_update(const GJArgs& j, GJShared<NT>& S, int
     const int li = lane & 15, lg = lane >> 4;
     const int n = j.n, np = (n + 15) >> 4;
     f64x4 acc[NT][CT];
-    if (j.mode == QSL_FP64) gjt_load<NT>((const double*)j.C + (size_t)w * 5 * n * n, n, u, lane, acc);
-    else gjt_load<NT>((const float*)j.C + (size_t)w * 5 * n * n, n, u, lane, acc);
+    if (j.mode == QSL_FP64) gjt_load<NT>((const double*)j.C + (size_t)w * j.c1_stride, n, u, lane, acc);
+    else gjt_load<NT>((const float*)j.C + (size_t)w * j.c1_stride, n, u, lane, acc);
     // pivot-row entries of this wave's columns, [k][16 ct + 4 (e % 4) + e / 4]
     double* pr = S.main + 3 * 16 * LS + u * 16 * PS;
     double* Xw = S.X() + lg * LS + li;

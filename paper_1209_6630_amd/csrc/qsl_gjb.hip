@@ -131,7 +131,7 @@ __device__ __forceinline__ void gjb_init_body(const Job& j, int w, int sub) {
     const int n = j.n;
     const size_t nn = (size_t)n * n;
     const GjbView v = gjb_view(j, w);
-    const Tin* __restrict__ C1 = (const Tin*)j.C + (size_t)w * 5 * nn;
+    const Tin* __restrict__ C1 = (const Tin*)j.C + (size_t)w * c1_stride(j);
     __shared__ double tile[32][33];
     const int tid = threadIdx.x;
     const int nt = (n + 31) >> 5;

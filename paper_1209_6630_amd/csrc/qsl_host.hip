@@ -775,7 +775,7 @@ hipError_t CallLists::store(hipStream_t st) const {
     return hipGetLastError();
 }
 
-static const char* contract_label(int mode) {
+const char* contract_label(int mode) {
     return mode == QSL_FP64 ? "contract_fp64" : mode == QSL_FP32 ? "contract_fp32" : "contract_bf16x3";
 }
 

@@ -361,8 +361,15 @@ struct Job {
     // (e, b) and walker group (e, g) take positions [32 b, 32 b + 32) and
     // [g gw, (g + 1) gw) (NULL: walker order)
     const int* wperm;
+    // Several determinants: the inversion's C_1 has walkers c1_stride values
+    // apart (0: 5 n n); the drift and Laplacian take column occ[i] of rows of
+    // c_ld MOs for column i (NULL: rows of n, column i)
+    int64_t c1_stride;
+    const int* occ;
+    int c_ld;
     int gx, gy, gz;          // the Job's grid in the current phase
 };
+__host__ __device__ inline int64_t c1_stride(const Job& j) { return j.c1_stride ? j.c1_stride : 5 * (int64_t)j.n * j.n; }
 // Bytes of the device Job copy of a per-system launch (Job, then two ints).
 constexpr size_t JOBSLOT_BYTES = (sizeof(Job) + 2 * sizeof(int) + 255) / 256 * 256;
 
@@ -503,6 +510,7 @@ struct CallLists {
     }
     hipError_t store(hipStream_t st) const;  // to the device, by one small kernel
 };
+const char* contract_label(int mode);  // the contraction's name in profiles
 
 struct WsLayout {
     size_t job_off;  // the device Job copy of per-system launches
@@ -570,6 +578,7 @@ int contract_per_cu(int mode, int tile);
 // Gauss-Jordan inversion, log|det| and sign (one block per matrix; the
 // block shape depends on n, so a batched launch serves one variant).
 constexpr int GJ_V_BLOCKED = 14;   // the variants below it are register-resident, n <= 16 (v + 1)
+constexpr int GJ_READ_PAST = 224;  // values the inversion may read past the last row of C_1
 constexpr int GJ_V_APPROX = 8;     // from this variant on pivots are compared to 2^-12
 int gj_variant(int n);
 int gj_job_variant(const Job& j);  // gj_variant(n) + gj_bias, clamped

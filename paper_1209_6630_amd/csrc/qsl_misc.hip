@@ -121,8 +121,10 @@ __device__ __forceinline__ void epilogue_body(const Job& j, int bx) {
     const int64_t w = row / n;
     const int e = (int)(row % n);
     const double* d = Dinv + (w * n + e) * n;
-    const size_t nn = (size_t)n * n;
-    const Tc* Cw = C + (size_t)w * 5 * nn + (size_t)e * n;
+    const int* __restrict__ occ = j.occ;
+    const int ld = occ ? j.c_ld : n;
+    const size_t nn = (size_t)n * ld;
+    const Tc* Cw = C + (size_t)w * 5 * nn + (size_t)e * ld;
     // G row of the dA by electron (FP32 mode with that adjoint)
     float* __restrict__ grow = j.g32 ? j.g32 + (size_t)(w * n + e) * g32_ld(n) : nullptr;
     const double gv = grow ? j.g[2 * w + spin] : 0.0;
@@ -136,8 +138,9 @@ __device__ __forceinline__ void epilogue_body(const Job& j, int bx) {
         for (int u = 0; u < 4; ++u) {
             const int i = min(i0 + 64 * u + lane, n - 1);
             di[u] = gmem(d)[i];
+            const int ci = occ ? gmem(occ)[i] : i;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) cv[u][c] = gmem(Cw)[(size_t)(c + 1) * nn + i];
+            for (int c = 0; c < 4; ++c) cv[u][c] = gmem(Cw)[(size_t)(c + 1) * nn + ci];
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)

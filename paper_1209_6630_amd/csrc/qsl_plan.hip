@@ -318,10 +318,6 @@ static const int* dev_prefix(const qsl_plan* p, const PhaseList& L) {
 static const Job* dev_jobs(const qsl_plan* p, int ph) { return dev_jobs(p, p->ph[ph]); }
 static const int* dev_prefix(const qsl_plan* p, int ph) { return dev_prefix(p, p->ph[ph]); }
 
-static const char* contract_name(int mode) {
-    return mode == QSL_FP64 ? "contract_fp64" : mode == QSL_FP32 ? "contract_fp32" : "contract_bf16x3";
-}
-
 // Enqueue one launch of the plan on st (no synchronisation, no allocation:
 // safe under stream capture).
 static qsl_status enqueue(qsl_plan* p, hipStream_t st) {
@@ -372,7 +368,7 @@ static qsl_status enqueue(qsl_plan* p, hipStream_t st) {
         }
         auto& C = p->ph[PH_CONTRACT];
         if (C.blocks()) {
-            ProfScope ps(contract_name(mode), st);
+            ProfScope ps(contract_label(mode), st);
             const int tile = C.jobs[0].f32_tile;
             unsigned* queue = nullptr;
             int grid = C.blocks();
@@ -410,7 +406,7 @@ static qsl_status enqueue(qsl_plan* p, hipStream_t st) {
             if ((e = launch_screen(j, 0, st)) != hipSuccess) return hip_fail(e, "screen kernel");
         }
         for (const Job& j : p->ph[PH_CONTRACT].jobs) {
-            ProfScope ps(contract_name(mode), st);
+            ProfScope ps(contract_label(mode), st);
             if ((e = launch_contract(j, st)) != hipSuccess) return hip_fail(e, "contraction kernel");
         }
         for (int v = 0; v <= GJ_V_BLOCKED; ++v)

@@ -32,3 +32,30 @@ def test_each_spin_as_by_itself(n_up, n_dn):
             np.testing.assert_array_equal(both[k][:, s], alone[k][:, 0])
         for k in ("drift", "lap"):
             np.testing.assert_array_equal(both[k][:, el], alone[k])
+
+
+@pytest.mark.parametrize("n_up,n_dn,n_det,W", [(12, 5, 40, 3), (33, 8, 7, 2), (9, 0, 3, 2), (130, 120, 3, 2), (230, 12, 2, 2)])
+def test_each_determinant_as_a_forward(n_up, n_dn, n_det, W):
+    """Determinants inverted in groups: each one's log|det| and sign bit for
+    bit those of a forward with its orbitals alone."""
+    import torch
+    print(f"[case] determinants n_up={n_up} n_dn={n_dn} n_det={n_det}", flush=True)
+    sysm, A_up, A_dn = random_tiny(n_atoms=(n_up + n_dn) // 6 + 2, n_up=n_up, n_dn=n_dn, seed=n_up)
+    rng = np.random.default_rng(n_up)
+    R = walkers_near(sysm, W, seed=n_up + 1)
+    orb = [np.concatenate([A, rng.normal(size=(4, A.shape[1])) / np.sqrt(A.shape[1])]) if len(A) else A for A in (A_up, A_dn)]
+    occ = np.array([np.concatenate([rng.permutation(len(o))[:n] for o, n in zip(orb, (n_up, n_dn))])
+                    for _ in range(n_det)], np.int32)
+    S = make_gpu_system(sysm, A_up, A_dn)
+    for s in range(2):
+        if len(orb[s]):
+            S.set_orbitals(s, orb[s])
+    out = S.multidet_forward(torch.from_numpy(R).cuda(), occ, rng.normal(size=n_det), "fp64")
+    T = make_gpu_system(sysm, A_up, A_dn)
+    for K in range(n_det):
+        T.set_mo(0, orb[0][occ[K, :n_up]])
+        if n_dn:
+            T.set_mo(1, orb[1][occ[K, n_up:]])
+        one = run_gpu_forward(T, R, "fp64")
+        np.testing.assert_array_equal(out["det_logdet"][K].cpu().numpy(), one["logdet"])
+        np.testing.assert_array_equal(out["det_sign"][K].cpu().numpy(), one["sign"])
