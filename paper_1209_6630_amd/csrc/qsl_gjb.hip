@@ -210,14 +210,49 @@ __device__ __forceinline__ uint64_t key_max_wave(uint64_t k) {
     return m;
 }
 
-// One thread per row b holds M[b][k0 .. k0 + NB) in registers.  The panel's
-// columns are unrolled at compile time, so the column being reduced and the
-// pivot entry are plain registers (no select over the row), and no column
-// leaves the sequence early (a column past the panel or after a failed
-// pivot changes nothing that is kept).  Per column: the wave's largest
-// pivot key, one barrier, the largest of the waves' keys (16-lane DPP),
-// then one FMA per entry, P -= f (pivot row), on every row; the pivot row's
-// own scaling by 1/pv is deferred to the store.
+// P[q] += c x[q], q < NB, for a row x in LDS that every lane takes whole: lane
+// l loads x[16 h + l % 16] and the products read it across the 16 lanes as
+// they go (row_newbcast), 2 LDS reads instead of NB / 2.  The wait states a
+// DPP operand needs after a write of its register stand before each group.
+template <int NB>
+__device__ __forceinline__ void fma_row(double (&P)[NB], const double* x, double c, int lane) {
+    static_assert(NB % 16 == 0, "whole 16-lane rows");
+#define QSL_BC(N) "v_fmac_f64_dpp %" #N ", %8, %9 row_newbcast:"
+#define QSL_BC8(A0, A1, A2, A3, A4, A5, A6, A7)                                             \
+    "s_nop 1\n" QSL_BC(0) #A0 " row_mask:0xf bank_mask:0xf\n" QSL_BC(1) #A1 " row_mask:0xf bank_mask:0xf\n" \
+    QSL_BC(2) #A2 " row_mask:0xf bank_mask:0xf\n" QSL_BC(3) #A3 " row_mask:0xf bank_mask:0xf\n"            \
+    QSL_BC(4) #A4 " row_mask:0xf bank_mask:0xf\n" QSL_BC(5) #A5 " row_mask:0xf bank_mask:0xf\n"            \
+    QSL_BC(6) #A6 " row_mask:0xf bank_mask:0xf\n" QSL_BC(7) #A7 " row_mask:0xf bank_mask:0xf"
+#pragma unroll
+    for (int h = 0; h < NB; h += 16) {
+        const double v = x[h + (lane & 15)];
+        asm(QSL_BC8(0, 1, 2, 3, 4, 5, 6, 7)
+            : "+v"(P[h]), "+v"(P[h + 1]), "+v"(P[h + 2]), "+v"(P[h + 3]), "+v"(P[h + 4]), "+v"(P[h + 5]), "+v"(P[h + 6]),
+              "+v"(P[h + 7])
+            : "v"(v), "v"(c));
+        asm(QSL_BC8(8, 9, 10, 11, 12, 13, 14, 15)
+            : "+v"(P[h + 8]), "+v"(P[h + 9]), "+v"(P[h + 10]), "+v"(P[h + 11]), "+v"(P[h + 12]), "+v"(P[h + 13]),
+              "+v"(P[h + 14]), "+v"(P[h + 15])
+            : "v"(v), "v"(c));
+    }
+#undef QSL_BC8
+#undef QSL_BC
+}
+
+// One thread per row b holds M[b][k0 .. k0 + NB) in registers, eight columns
+// unrolled at a time and then rotated to the front, so that the column being
+// reduced and the pivot entry are plain registers; no column leaves the
+// sequence early (a column past the panel or after a failed pivot changes
+// nothing that is kept).  Per column: the wave's largest pivot key, a barrier,
+// the largest of the waves' keys (16-lane DPP); the pivot row's wave alone
+// stores it with 1/pv, a barrier, then one FMA per entry, P -= f (pivot row),
+// on every row; the pivot row's own scaling by 1/pv is deferred to the store.
+// Bound by the products' FP64 issue with the row read across lanes (128 per
+// SIMD and column) and the two barriers: 3700 cycles a column, 100 us a first
+// and 153 us a second panel of 256 matrices at n = 866.  Every wave storing its
+// candidate row before one barrier, each a store of 32 entries by one lane,
+// and 16 LDS reads of the row per wave: the whole inversion of 1024 matrices
+// 64.2 ms instead of 60.0.
 // SECOND: the second panel B = [k0, k0 + NB) of a pass, after the first
 // A = [k0 - NB, k0).  B's columns first take A's steps (rank NB: the rows
 // of A's pivots zeroed, plus L_A times A's pivot rows in B's columns, kept
@@ -234,8 +269,9 @@ __device__ __forceinline__ void gjb_panel_body(const Job& j, int w, int k0, int 
     if (k0 >= n) return;
     const GjbView v = gjb_view(j, w);
     if (v.st->flag) return;  // singular earlier: nothing left to do
-    __shared__ uint64_t cand_k[2][PW];
-    __shared__ double cand_row[2][PW][NB];
+    __shared__ uint64_t cand_k[PW];
+    __shared__ __attribute__((aligned(16))) double prow[NB];  // the pivot row
+    __shared__ double pinv;                                   // 1 / its entry in the column
     __shared__ int perm_l[NB];
     __shared__ double piv_l[NB];
     // SECOND: T_A[k][q] = M[p^A_k][k0 + q] (A's pivot rows in B's columns),
@@ -283,7 +319,7 @@ __device__ __forceinline__ void gjb_panel_body(const Job& j, int w, int k0, int 
         // + L_A[b][k] T_A[k][.]: L_A is this row's entries in A's columns,
         // taken eight at a time (bounded live registers)
         const double* rowA = v.M + (size_t)bl * v.ld + k0 - NB;
-#pragma unroll
+#pragma unroll 1
         for (int kc = 0; kc < NB; kc += 8) {
             double a[8];
 #pragma unroll
@@ -293,76 +329,75 @@ __device__ __forceinline__ void gjb_panel_body(const Job& j, int w, int k0, int 
                 a[i + 1] = b < n ? x.y : 0.0;
             }
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                static_for<0, NB / 8>([&](auto cc) __attribute__((always_inline)) {
-                    constexpr int c0 = decltype(cc)::value * 8;
-                    double t[8];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) t[q] = blk[kc + i][c0 + q];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) P[c0 + q] = fma(a[i], t[q], P[c0 + q]);
-                    __builtin_amdgcn_sched_barrier(0);
-                });
+            for (int i = 0; i < 8; ++i) fma_row<NB>(P, blk[kc + i], a[i], lane);
         }
     }
+    constexpr int KG = 8;  // columns unrolled at a time
     double sc = 1.0;   // the row's pending scale (1/pv once it is a pivot row)
     bool newpiv = false;  // the row is a pivot row of this panel
     int fail = 0;      // uniform: 1 no pivot (zero column), 2 non-finite pivot
-    static_for<0, NB>([&](auto kc) __attribute__((always_inline)) {
-        constexpr int k = decltype(kc)::value, buf = k & 1;
-        const bool live = k < kn && !fail;  // uniform
-        const uint64_t wk = key_max_wave(pivot_key(P[k], b, !used));
-        if (b == 0x3FF - (int)(wk & 0x3FF) && wk != 0) {
+#pragma unroll 1
+    for (int kg = 0; kg < NB; kg += KG) {
+        static_for<0, KG>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int kk = decltype(kc)::value;
+            const int k = kg + kk;
+            const bool live = k < kn && !fail;  // uniform
+            const uint64_t wk = key_max_wave(pivot_key(P[kk], b, !used));
+            if (lane == 0) cand_k[wave] = wk;
+            __syncthreads();
+            uint64_t top = key_max_row(lane < PW ? cand_k[lane] : 0ull);
+            top = readlane_u64(top, 0);
+            const double topv = __longlong_as_double((long long)(top & ~0x3FFull));
+            const int bad = !(topv > 0.0) ? 1 : (!isfinite(topv) ? 2 : 0);
+            if (live && bad) {
+                if (tid == 0) gmem(v.st)->flag = bad;
+                fail = bad;
+            }
+            const int p = 0x3FF - (int)(top & 0x3FF);  // the pivot row (any row when bad)
+            if (wave == p >> 6) {
+                const double iv = 1.0 / P[kk];
+                if (b == p) {
 #pragma unroll
-            for (int q = 0; q < NB; ++q) cand_row[buf][wave][q] = P[q];
-        }
-        if (lane == 0) cand_k[buf][wave] = wk;
-        __syncthreads();
-        uint64_t top = key_max_row(lane < PW ? cand_k[buf][lane] : 0ull);
-        top = readlane_u64(top, 0);
-        const double topv = __longlong_as_double((long long)(top & ~0x3FFull));
-        const int bad = !(topv > 0.0) ? 1 : (!isfinite(topv) ? 2 : 0);
-        if (live && bad) {
-            if (tid == 0) gmem(v.st)->flag = bad;
-            fail = bad;
-        }
-        const int p = 0x3FF - (int)(top & 0x3FF);  // the pivot row (any row when bad)
-        const int pw = min(p >> 6, PW - 1);         // its wave
-        const double pv = cand_row[buf][pw][k];
-        const double inv = 1.0 / pv;
-        const bool go = live && !bad;  // uniform
-        if (tid == 0 && go) {
-            perm_l[k] = p;
-            piv_l[k] = pv;
-        }
-        const bool piv = go && b == p;
-        // other rows: P -= f (pivot row), P[k] = -f with f = P[k] / pv.  The
-        // pivot row's scaling by 1/pv is kept aside in sc and applied when
-        // the panel is stored: its later updates are the same in the scaled
-        // and the unscaled form (f is a ratio of its own entries), and rows
-        // not yet used, which decide the pivots, never see it.  Nothing
-        // changes unless go.
-        const double f = (go && !piv) ? P[k] * inv : 0.0;
-        if (go) {
-            // the pivot row in chunks of 8 (bounded live registers)
-            static_for<0, NB / 8>([&](auto cc) __attribute__((always_inline)) {
-                constexpr int c0 = decltype(cc)::value * 8;
-                double pr[8];
+                    for (int q = 0; q < NB; ++q) prow[q] = P[q];
+                    pinv = iv;
+                }
+            }
+            __syncthreads();
+            const double pv = prow[kk];
+            const double inv = pinv;
+            const bool go = live && !bad;  // uniform
+            if (tid == 0 && go) {
+                perm_l[k] = p;
+                piv_l[k] = pv;
+            }
+            const bool piv = go && b == p;
+            // other rows: P -= f (pivot row), P[kk] = -f with f = P[kk] / pv.  The
+            // pivot row's scaling by 1/pv is kept aside in sc and applied when
+            // the panel is stored: its later updates are the same in the scaled
+            // and the unscaled form (f is a ratio of its own entries), and rows
+            // not yet used, which decide the pivots, never see it.  Nothing
+            // changes unless go.
+            const double f = (go && !piv) ? P[kk] * inv : 0.0;
+            if (go) {
+                fma_row<NB>(P, prow, -f, lane);
+                // the pivot row: 1/pv in column k, i.e. 1 before its scaling
+                P[kk] = piv ? 1.0 : -f;
+            }
+            if (piv) {
+                used = true;
+                newpiv = true;
+                sc = inv;
+            }
+        });
+        // the next columns to the front
+        double h[KG];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) pr[q] = cand_row[buf][pw][c0 + q];
+        for (int q = 0; q < KG; ++q) h[q] = P[q];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) P[c0 + q] = fma(-f, pr[q], P[c0 + q]);
-                __builtin_amdgcn_sched_barrier(0);
-            });
-            // the pivot row: 1/pv in column k, i.e. 1 before its scaling
-            P[k] = piv ? 1.0 : -f;
-        }
-        if (piv) {
-            used = true;
-            newpiv = true;
-            sc = inv;
-        }
-    });
+        for (int q = 0; q < NB - KG; ++q) P[q] = P[q + KG];
+#pragma unroll
+        for (int q = 0; q < KG; ++q) P[NB - KG + q] = h[q];
+    }
     if (fail) return;
     // the pivot order and row flags, written once the panel is done (a
     // generic store in the column loop would make every later LDS wait
@@ -379,29 +414,23 @@ __device__ __forceinline__ void gjb_panel_body(const Job& j, int w, int k0, int 
             blk[k][c] = k < kn ? v.M[(size_t)perm_l[k] * v.ld + k0 - NB + c] : 0.0;
         }
         __syncthreads();
-        if (b < n) {
-            double* rowA = v.M + (size_t)b * v.ld + k0 - NB;
-            // eight of A's columns at a time
+        // sixteen of A's columns at a time (every lane takes part: the
+        // products read across lanes)
+        double* rowA = v.M + (size_t)bl * v.ld + k0 - NB;
+#pragma unroll 1
+        for (int c0 = 0; c0 < NB; c0 += 16) {
+            double x[16];
 #pragma unroll
-            for (int c0 = 0; c0 < NB; c0 += 8) {
-                double x[8];
+            for (int q = 0; q < 16; q += 2) {
+                const f64x2 y = *gmem((const f64x2*)(rowA + c0 + q));
+                x[q] = newpiv ? 0.0 : y.x;
+                x[q + 1] = newpiv ? 0.0 : y.y;
+            }
 #pragma unroll
-                for (int q = 0; q < 8; q += 2) {
-                    const f64x2 y = *gmem((const f64x2*)(rowA + c0 + q));
-                    x[q] = newpiv ? 0.0 : y.x;
-                    x[q + 1] = newpiv ? 0.0 : y.y;
-                }
+            for (int k = 0; k < NB; ++k) fma_row<16>(x, blk[k] + c0, P[k], lane);
+            if (b < n) {
 #pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    double t[8];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) t[q] = blk[k][c0 + q];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) x[q] = fma(P[k], t[q], x[q]);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-#pragma unroll
-                for (int q = 0; q < 8; q += 2) *gmem((f64x2*)(rowA + c0 + q)) = f64x2{x[q], x[q + 1]};
+                for (int q = 0; q < 16; q += 2) *gmem((f64x2*)(rowA + c0 + q)) = f64x2{x[q], x[q + 1]};
             }
         }
     }
