@@ -86,9 +86,9 @@ def work_per_step(sysm, nnz, W, mode, tile=2):
     cpeak = PEAK["bf16x3"] if mode == "fp32" and tile == 2 else PEAK[mode]
     return {
         f"contract_{mode}": (contract, cpeak[0], cpeak[1], "TFLOP/s"),
-        # n <= 224: register-resident elimination on FP64 vector FMAs; larger
-        # n: blocked, with the rank-32 updates on FP64 MFMA
-        "gauss_jordan": (gj, "mfma" if max(ns) > 224 else "alu", PEAK_FP64, "TFLOP/s"),
+        # n <= 224: register-resident; larger n: blocked; both apply their
+        # panels' updates on FP64 MFMA
+        "gauss_jordan": (gj, "mfma", PEAK_FP64, "TFLOP/s"),
         "adjoint_h": (adjoint, PEAK[mode][0], PEAK[mode][1], "TFLOP/s"),
         # the FP32 dA by electron follows the contraction's tile
         "adjoint_dA": (adjoint, cpeak[0], cpeak[1], "TFLOP/s"),

@@ -257,7 +257,7 @@ typedef struct {
     int32_t batched;    /* 1: one launch per phase over the work list of all
                            systems; 0: one launch per system and spin       */
     int32_t adj_group;  /* walkers per dA group of the adjoint, 1..4096;
-                           0: min(W, 1024) for the FP32 dA by electron,
+                           0: min(W, 1024) for the dA by electron (FP32, FP64),
                            min(W, 128) for the dA by 32-electron range     */
     int32_t gj_bias;    /* 0: the smallest Gauss-Jordan block shape holding
                            n; 1: the next larger one (when there is one)      */

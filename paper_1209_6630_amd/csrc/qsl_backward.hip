@@ -1134,6 +1134,171 @@ __device__ __forceinline__ void adj_dae_s3_body(const Job& j, int bx, int by) {
     }
 }
 
+// ------------------------------------------------- dA by electron (FP64)
+// The same on v_mfma_f64_16x16x4f64: dA[i][slot] += D^-1_w[e][i] (g_w chi).
+// One 256-thread workgroup per (electron, walker group, chunk stride, 224
+// MOs), chunks of 64 slots: wave v keeps the block of 14 MO tiles x 16 slots
+// in its accumulators.  A batch of 32 walkers' rows of D^-1 is copied into LDS
+// (4-byte pieces: rows of an odd n are only 8-byte aligned) while each lane
+// evaluates the AO values that it itself holds as the products' operand (slot
+// lane % 16, walkers 4 ks + lane / 16), so no value passes through LDS and
+// none is computed twice.  Walkers with g = 0 get zeros for their row (D^-1
+// of a singular walker is NaN).  Rows of 240: a half-wave's two operand rows
+// lie in the two halves of the banks.
+// Bound by FP64 issue (the values' exponentials and the products share the
+// unit): 434 electrons x 1024 walkers 3.7 ms, by 32-electron range, which
+// evaluates 3.6x the group's slots, 8.0 ms; groups of 512 or 256 walkers 3.5
+// and 3.6 ms.
+constexpr int DF_NS = 64;   // slots per chunk (four waves x 16)
+constexpr int DF_MT = ADJ_MB / 16;
+constexpr int DF_LD = ADJ_MB + 16;
+
+__device__ __forceinline__ double slot_value64(const SlotR64& r, const SlotRec64* __restrict__ rec, double T_thr, double px,
+                                               double py, double pz) {
+    const double X = px - r.x, Y = py - r.y, Z = pz - r.z;
+    const double r2 = dist2_exact(X, Y, Z);
+    double g = 0.0;
+    auto prim = [&](double gk, double ck) __attribute__((always_inline)) {
+        const double t = mul_exact(gk, r2);
+        if (t <= T_thr) g += ck * exp_t(-t);
+    };
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        if (k < r.np) prim(r.ex[k], r.c[k]);
+#pragma unroll 1
+    for (int k = 3; k < r.np; ++k) prim(gmem(rec)->ex[k], gmem(rec)->c64[k]);
+    double p1, p2, p3, d, d2;
+    axis_pow(r.pw & 15, X, p1, d, d2);
+    axis_pow((r.pw >> 4) & 15, Y, p2, d, d2);
+    axis_pow((r.pw >> 8) & 15, Z, p3, d, d2);
+    return r.f * p2 * p3 * p1 * g;
+}
+
+__device__ __forceinline__ void adj_daf_body(const Job& j, int bx, int by) {
+    const DevSys& s = j.s;
+    const int n = j.n, gw = j.gw;
+    const int64_t W = j.W;
+    const int ngw = (int)((W + gw - 1) / gw);
+    // the XCD-aware block mapping of adj_dae_body
+    const int o = bx & 31;
+    const int grp = (bx >> 5) * 8 + (o & 7), cs = o >> 3;
+    if (grp >= n * ngw) return;
+    const int e = grp / ngw, gi = grp % ngw;
+    const int nsl = j.gnwin[grp];
+    if (cs * DF_NS >= nsl) return;
+    const int* __restrict__ sl = j.gwin + (size_t)grp * WIN * s.n_win;
+    const int64_t w0 = (int64_t)gi * gw;
+    const int nw = (int)min<int64_t>(gw, W - w0);
+    const int i0 = by * ADJ_MB, mine = min(ADJ_MB, n - i0), nt = (mine + 15) >> 4;
+    const int N = s.n_up + s.n_dn, eoff = j.spin ? s.n_up : 0;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const double Tscr = readlane_f64(s.T, 0);
+    const double* __restrict__ Dinv = j.Dinv;
+    const double* __restrict__ R = j.R;
+    const double* __restrict__ gl = j.g;
+
+    __shared__ double ep[DE_KW][3];
+    __shared__ double gv[DE_KW];
+    __shared__ int wl[DE_KW];  // the batch's walkers (past the group: its last)
+    __shared__ __attribute__((aligned(16))) double G[DE_KW * DF_LD];
+
+    for (int c0 = cs * DF_NS; c0 < nsl; c0 += DE_NCH * DF_NS) {
+        const int q = c0 + 16 * wave + li;
+        const bool live = q < nsl, busy = c0 + 16 * wave < nsl;  // busy: uniform
+        const int slot = sl[min(q, nsl - 1)];
+        const SlotRec64* rec = s.slot_rec64 + slot;
+        SlotR64 rg;
+        rg.load(rec);
+        f64x4 acc[DF_MT];
+#pragma unroll
+        for (int t = 0; t < DF_MT; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int wb = 0; wb < nw; wb += DE_KW) {
+            const int kw = min(DE_KW, nw - wb);
+            __syncthreads();  // the previous batch's products are done with G, ep, gv and wl
+            if (tid < DE_KW * 3) {
+                const int64_t w = walker_of(j.wperm, W, e, w0 + wb + min(tid / 3, kw - 1));
+                ep[tid / 3][tid % 3] = R[((size_t)w * N + eoff + e) * 3 + tid % 3];
+            } else if (tid < DE_KW * 4) {
+                const int k = tid - DE_KW * 3;
+                const int64_t w = walker_of(j.wperm, W, e, w0 + wb + min(k, kw - 1));
+                wl[k] = (int)w;
+                gv[k] = gl[2 * w + j.spin];
+            }
+            __syncthreads();
+            bool zero = false;  // a row of this wave belongs to a walker with g = 0
+#pragma unroll 1
+            for (int r = 8 * wave; r < 8 * wave + 8; ++r) {
+                const float* src = (const float*)(Dinv + ((size_t)wl[r] * n + e) * n + i0);
+                zero |= gv[r] == 0.0;
+#pragma unroll
+                for (int t = 0; t < ADJ_MB * 2 / 64; ++t)
+                    if (64 * t < 2 * mine)
+                        __builtin_amdgcn_global_load_lds((const void*)(src + min(64 * t + lane, 2 * mine - 1)),
+                                                         (__attribute__((address_space(3))) void*)((char*)&G[r * DF_LD] + 256 * t),
+                                                         4, 0, 0);
+            }
+            double B[DE_KW / 4];
+            if (busy) {
+#pragma unroll 1
+                for (int ks = 0; ks < DE_KW / 4; ++ks) {
+                    const int k = 4 * ks + lg;
+                    double v = 0.0;
+                    if (live && k < kw) v = gv[k] * slot_value64(rg, rec, Tscr, ep[k][0], ep[k][1], ep[k][2]);
+                    // B[ks] after the last one: the array moves down a place at a time
+#pragma unroll
+                    for (int i = 0; i + 1 < DE_KW / 4; ++i) B[i] = B[i + 1];
+                    B[DE_KW / 4 - 1] = v;
+                }
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's copies into LDS have landed
+            if (zero)
+#pragma unroll 1
+                for (int r = 8 * wave; r < 8 * wave + 8; ++r)
+                    if (gv[r] == 0.0)
+                        for (int i = lane; i < ADJ_MB; i += 64) G[r * DF_LD + i] = 0.0;
+            __syncthreads();
+            if (!busy) continue;
+            const double* a = G + lg * DF_LD + li;
+#pragma unroll
+            for (int ks = 0; ks < DE_KW / 4; ++ks) {
+                static_for<0, 3>([&](auto gc) __attribute__((always_inline)) {
+                    constexpr int t0 = decltype(gc)::value * 5, t1 = t0 + 5 < DF_MT ? t0 + 5 : DF_MT;
+                    if (t0 == 0 || nt > t0) {
+#pragma unroll
+                        for (int t = t0; t < t1; ++t)
+                            acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[4 * ks * DF_LD + 16 * t], B[ks], acc[t], 0, 0, 0);
+                    }
+                });
+                if (ks & 1) __builtin_amdgcn_sched_barrier(0);  // bounded live operands
+            }
+        }
+        // flush: 16 lanes of a register cover 16 slots of one MO row
+        if (live) {
+            const int ao = s.slot_ao[slot];
+            // (base and row limit opaque, as in adj_dae_body)
+            int nbas = __builtin_amdgcn_readfirstlane(s.n_basis), lim = mine - lg;  // rows di < lim of lane row lg exist
+            asm volatile("" : "+s"(nbas));
+            asm volatile("" : "+v"(lim));
+            double* col = j.dA64 + (size_t)(i0 + lg) * nbas + max(ao, 0);
+#pragma unroll
+            for (int t = 0; t < DF_MT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int di = 16 * t + 4 * r;
+                    const double v = acc[t][r];
+                    if (di < lim && ao >= 0 && v != 0.0) atomicAdd(col + (size_t)di * nbas, v);
+                }
+        }
+    }
+}
+
+__global__ __launch_bounds__(DE_THREADS, 2) void adj_daf_kernel(Job j) { adj_daf_body(j, blockIdx.x, blockIdx.y); }
+
+__global__ __launch_bounds__(DE_THREADS, 2) void adj_daf_batched(const Job* jobs, const int* prefix, int njobs) {
+    batch_block(jobs, prefix, njobs, [&](const Job& j, int bx, int by, int) { adj_daf_body(j, bx, by); });
+}
+
 __global__ __launch_bounds__(DE_THREADS, 2) void adj_dae_kernel(Job j) { adj_dae_body(j, blockIdx.x, blockIdx.y); }
 
 __global__ __launch_bounds__(DE_THREADS, 2) void adj_dae_batched(const Job* jobs, const int* prefix, int njobs) {
@@ -1154,17 +1319,19 @@ void adj_dae_grid(Job& j) {
 
 hipError_t launch_adj_dae(const Job& j0, hipStream_t st) {
     Job j = j0;
-    if (j.gw < 1 || j.mode != QSL_FP32 || !j.by_e || (j.n && j.W && j.dA32 && !j.g32)) return hipErrorInvalidValue;
+    if (j.gw < 1 || j.mode == QSL_BF16X3 || !j.by_e || (j.n && j.W && j.dA32 && !j.g32)) return hipErrorInvalidValue;
     adj_dae_grid(j);
-    if (!j.n || !j.W || !j.dA32) return hipSuccess;
-    if (j.f32_tile == 2) adj_dae_s3_kernel<<<dim3((unsigned)j.gx, j.gy), DE_THREADS, 0, st>>>(j);
+    if (!j.n || !j.W || (!j.dA32 && !j.dA64)) return hipSuccess;
+    if (j.mode == QSL_FP64) adj_daf_kernel<<<dim3((unsigned)j.gx, j.gy), DE_THREADS, 0, st>>>(j);
+    else if (j.f32_tile == 2) adj_dae_s3_kernel<<<dim3((unsigned)j.gx, j.gy), DE_THREADS, 0, st>>>(j);
     else adj_dae_kernel<<<dim3((unsigned)j.gx, j.gy), DE_THREADS, 0, st>>>(j);
     return hipGetLastError();
 }
 
-hipError_t launch_adj_dae_batched(int tile, const Job* jobs, const int* prefix, int njobs, int grid, hipStream_t st) {
+hipError_t launch_adj_dae_batched(int mode, int tile, const Job* jobs, const int* prefix, int njobs, int grid, hipStream_t st) {
     if (grid <= 0) return hipSuccess;
-    if (tile == 2) adj_dae_s3_batched<<<grid, DE_THREADS, 0, st>>>(jobs, prefix, njobs);
+    if (mode == QSL_FP64) adj_daf_batched<<<grid, DE_THREADS, 0, st>>>(jobs, prefix, njobs);
+    else if (tile == 2) adj_dae_s3_batched<<<grid, DE_THREADS, 0, st>>>(jobs, prefix, njobs);
     else adj_dae_batched<<<grid, DE_THREADS, 0, st>>>(jobs, prefix, njobs);
     return hipGetLastError();
 }

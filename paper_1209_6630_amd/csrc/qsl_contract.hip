@@ -561,27 +561,7 @@ struct F64T {
     static constexpr int EPT = TE / (THREADS / KC);     // electrons per thread of the evaluation
 };
 
-// rec_values of one slot, its record's first primitives in registers.
-struct SlotR64 {
-    double x, y, z, f;
-    double ex[3], c[3];
-    int pw, np;
-    __device__ __forceinline__ void load(const SlotRec64* r) {
-        typedef __attribute__((ext_vector_type(2))) double f64x2;
-        const f64x2 a = *gmem((const f64x2*)&r->pos[0]), b = *gmem((const f64x2*)&r->pos[2]);
-        const f64x2 e0 = *gmem((const f64x2*)&r->ex[0]), e1 = *gmem((const f64x2*)&r->ex[2]);
-        const f64x2 c0 = *gmem((const f64x2*)&r->c64[0]), c1 = *gmem((const f64x2*)&r->c64[2]);
-        typedef __attribute__((ext_vector_type(2))) int i32x2;
-        const i32x2 t = *gmem((const i32x2*)&r->pw);
-        x = a.x; y = a.y; z = b.x; f = b.y;
-        ex[0] = e0.x; ex[1] = e0.y; ex[2] = e1.x;
-        c[0] = c0.x; c[1] = c0.y; c[2] = c1.x;
-        pw = t.x; np = t.y;
-    }
-};
-static_assert(offsetof(SlotRec64, pos) == 0 && offsetof(SlotRec64, f64) == 24 && offsetof(SlotRec64, np) == offsetof(SlotRec64, pw) + 4,
-              "slot record layout read by SlotR64::load");
-
+// rec_values of one slot, its record in registers.
 __device__ __forceinline__ void slot_values64(const SlotR64& r, const SlotRec64* __restrict__ rec, double T_thr,
                                               const double p[3], double v[5], bool& tie) {
     const double X = p[0] - r.x, Y = p[1] - r.y, Z = p[2] - r.z;

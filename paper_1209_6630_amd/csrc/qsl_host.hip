@@ -178,7 +178,7 @@ WsLayout ws_layout(const DevSys& d, int64_t W, int gw, int mode, bool by_e) {
     for (int s = 0; s < 2; ++s) {
         const int n = n_spin(d, s);
         L.g32_off[s] = off;
-        if (by_e && n) off = round_up(off + (size_t)W * n * g32_ld(n) * sizeof(float), 256);
+        if (by_e && mode == QSL_FP32 && n) off = round_up(off + (size_t)W * n * g32_ld(n) * sizeof(float), 256);
     }
     L.total = std::max<size_t>(off, 256);
     return L;
@@ -238,7 +238,7 @@ Job bwd_job(qsl_system* sys, const qsl_bwd_args* a, const WsLayout& L, char* ws,
         if (a->mode == QSL_FP64) j.dA64 = a->dA[s];
         else j.dA32 = (float*)(ws + L.dA32_off[s]);
         if (a->mode == QSL_BF16X3) j.gsplit = (uint16_t*)(ws + L.gs_off[s]);
-        if (by_e) j.g32 = (float*)(ws + L.g32_off[s]);
+        if (by_e && a->mode == QSL_FP32) j.g32 = (float*)(ws + L.g32_off[s]);
     }
     j.f32_tile = F32_TILE_DEFAULT;
     return j;
@@ -958,7 +958,7 @@ qsl_status qsl_backward(qsl_system* sys, const qsl_bwd_args* a, void* stream) {
         // the slot lists of the (electron, walker group) pairs, or the window
         // lists of the groups
         P.add(GROUP, s, by_e ? group_slots_blocks(j) : screen_blocks(j, 1));
-        if (by_e) P.add(G, s, g32_blocks(j));
+        if (j.g32) P.add(G, s, g32_blocks(j));
         else if (j.gsplit) P.add(G, s, gsplit_blocks(j));
         Job t = j;
         if (by_e) adj_dae_grid(t);
@@ -1003,7 +1003,7 @@ qsl_status qsl_backward(qsl_system* sys, const qsl_bwd_args* a, void* stream) {
     if (P.any(DA)) {
         ProfScope ps("adjoint_dA", st);
         e = P.run(DA, [&](const Job* js, const int* pre, int nj, int nb) {
-            return by_e ? launch_adj_dae_batched(F32_TILE_DEFAULT, js, pre, nj, nb, st)
+            return by_e ? launch_adj_dae_batched(a->mode, F32_TILE_DEFAULT, js, pre, nj, nb, st)
                         : launch_adj_da_batched(a->mode, js, pre, nj, nb, st);
         });
         if (e != hipSuccess) return hip_fail(e, "adjoint dA kernel");

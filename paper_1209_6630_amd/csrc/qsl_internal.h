@@ -458,9 +458,9 @@ hipError_t fill_f64(double* p, double v, int64_t n, hipStream_t st);
 int bw_group(int64_t W, bool by_e);
 // The adjoint's dA runs by electron index (walker groups of one electron,
 // an exact slot list per group, walkers as the contraction dimension) in
-// FP32 unless the deterministic reduction is asked for; by 32-electron
-// ranges otherwise.
-inline bool dA_by_electron(int mode, bool det) { return mode == QSL_FP32 && !det; }
+// FP32 and FP64 unless the deterministic reduction is asked for; by
+// 32-electron ranges otherwise.
+inline bool dA_by_electron(int mode, bool det) { return mode != QSL_BF16X3 && !det; }
 
 // Workspace of one system: byte offsets of the per-spin tile and group
 // window lists and of the FP32 dA accumulator.
@@ -473,6 +473,27 @@ constexpr int ADJ_NIB = ADJ_MB / 32;
 __host__ __device__ inline int64_t gsplit_elems(int n) {
     return (int64_t)((n + TE - 1) / TE) * ((n + ADJ_MB - 1) / ADJ_MB * ADJ_MB) * TE;
 }
+
+// An FP64 slot record with its first primitives in registers.
+struct SlotR64 {
+    double x, y, z, f;
+    double ex[3], c[3];
+    int pw, np;
+    __device__ __forceinline__ void load(const SlotRec64* r) {
+        typedef __attribute__((ext_vector_type(2))) double f64x2;
+        const f64x2 a = *gmem((const f64x2*)&r->pos[0]), b = *gmem((const f64x2*)&r->pos[2]);
+        const f64x2 e0 = *gmem((const f64x2*)&r->ex[0]), e1 = *gmem((const f64x2*)&r->ex[2]);
+        const f64x2 c0 = *gmem((const f64x2*)&r->c64[0]), c1 = *gmem((const f64x2*)&r->c64[2]);
+        typedef __attribute__((ext_vector_type(2))) int i32x2;
+        const i32x2 t = *gmem((const i32x2*)&r->pw);
+        x = a.x; y = a.y; z = b.x; f = b.y;
+        ex[0] = e0.x; ex[1] = e0.y; ex[2] = e1.x;
+        c[0] = c0.x; c[1] = c0.y; c[2] = c1.x;
+        pw = t.x; np = t.y;
+    }
+};
+static_assert(offsetof(SlotRec64, pos) == 0 && offsetof(SlotRec64, f64) == 24 && offsetof(SlotRec64, np) == offsetof(SlotRec64, pw) + 4,
+              "slot record layout read by SlotR64::load");
 
 // Job lists of a call on one system: both spins in one launch per phase.
 constexpr int CALL_PHASES = 8;
@@ -632,11 +653,11 @@ hipError_t launch_adj_h_batched(int mode, const Job* jobs, const int* prefix, in
                                    hipStream_t st);
 hipError_t launch_adj_da_batched(int mode, const Job* jobs, const int* prefix, int njobs, int grid,
                                     hipStream_t st);
-// dA by electron (FP32, Job.by_e): grid (electron x walker group x chunk
+// dA by electron (FP32 and FP64, Job.by_e): grid (electron x walker group x chunk
 // stride, MO blocks of 224) over the group slot lists.
 void adj_dae_grid(Job& j);
 hipError_t launch_adj_dae(const Job& j, hipStream_t st);
-hipError_t launch_adj_dae_batched(int tile, const Job* jobs, const int* prefix, int njobs, int grid, hipStream_t st);
+hipError_t launch_adj_dae_batched(int mode, int tile, const Job* jobs, const int* prefix, int njobs, int grid, hipStream_t st);
 hipError_t launch_finalize_dA(const float* dA32, double* dA, int64_t count, int accumulate, hipStream_t st);
 // dA = [dA +] sum_p part[p] (p ascending; float or double partials).
 hipError_t launch_reduce_dA(const void* part, bool fp64, int npart, int64_t count, double* dA, int accumulate,

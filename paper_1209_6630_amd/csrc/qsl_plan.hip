@@ -89,7 +89,7 @@ static void drop_graph(qsl_plan* p) {
     p->graph = nullptr;
 }
 
-// The plan's dA runs by electron (FP32 without det_dA, systems whose
+// The plan's dA runs by electron (FP32 and FP64 without det_dA, systems whose
 // windows fit the slot screen's bitmap) or by 32-electron range.
 static bool plan_by_e(const qsl_plan* p, int i) {
     return dA_by_electron(p->mode, p->tune.det_dA != 0) && p->sys[i]->d.n_win <= UNION_MAXWIN;
@@ -244,7 +244,7 @@ static qsl_status prepare(qsl_plan* p, hipStream_t st) {
             p->ph[PH_SLOTS_G].jobs.push_back(j);
             bool g_written = false;
             for (const Job& ej : p->ph[PH_EPILOGUE].jobs) g_written |= ej.g32 == b.g32;
-            if (!g_written) {
+            if (b.g32 && !g_written) {
                 j = b;
                 j.gx = g32_blocks(j); j.gy = 1; j.gz = 1;
                 p->ph[PH_G32].jobs.push_back(j);
@@ -497,8 +497,8 @@ static qsl_status enqueue(qsl_plan* p, hipStream_t st) {
         auto& DE = p->ph[PH_ADJ_DAE];
         if (DE.blocks()) {
             ProfScope ps("adjoint_dA", st);
-            if ((e = launch_adj_dae_batched(p->tune.contract_tile, dev_jobs(p, PH_ADJ_DAE), dev_prefix(p, PH_ADJ_DAE), (int)DE.jobs.size(),
-                                            DE.blocks(), st)) != hipSuccess)
+            if ((e = launch_adj_dae_batched(mode, p->tune.contract_tile, dev_jobs(p, PH_ADJ_DAE),
+                                            dev_prefix(p, PH_ADJ_DAE), (int)DE.jobs.size(), DE.blocks(), st)) != hipSuccess)
                 return hip_fail(e, "adjoint dA kernel");
         }
         auto& GS = p->ph[PH_GSPLIT];
