@@ -131,14 +131,15 @@ int bw_group(int64_t W, bool by_e) { return (int)std::min<int64_t>(W, by_e ? 102
 // (windows per 32-electron range, or slots per electron with by_e), the
 // FP32 dA accumulator and the split-BF16 G.  A forward-only workspace ends
 // at fwd_total.
-WsLayout ws_layout(const DevSys& d, int64_t W, int gw, int mode, bool by_e) {
+WsLayout ws_layout(const DevSys& d, int64_t W, int gw, int mode, bool by_e, bool sort) {
     WsLayout L{};
     size_t off = 0;
     L.job_off = off;
     off += JOBSLOT_BYTES;
+    L.sorted = sort && walker_sorted(d, mode, W);
     for (int s = 0; s < 2; ++s) {
         L.perm_off[s] = off;
-        if (mode == QSL_FP32) off = round_up(off + (size_t)n_spin(d, s) * W * sizeof(int), 256);
+        if (L.sorted) off = round_up(off + (size_t)n_spin(d, s) * W * sizeof(int), 256);
     }
     for (int s = 0; s < 2; ++s) {
         int n = n_spin(d, s);
@@ -198,7 +199,7 @@ Job fwd_job(qsl_system* sys, const qsl_fwd_args* a, const WsLayout& L, char* ws,
     j.nwin = (int*)(ws + L.nwin_off[s]);
     j.win = (int*)(ws + L.win_off[s]);
     j.jobslot = ws + L.job_off;
-    if (sorted && a->mode == QSL_FP32) j.wperm = (const int*)(ws + L.perm_off[s]);
+    if (sorted && L.sorted) j.wperm = (const int*)(ws + L.perm_off[s]);
     j.f32_tile = F32_TILE_DEFAULT;
     j.C = a->C[s];
     if (gj_blocked(j.n)) j.gjws = (double*)(ws + L.gj_off[s]);
@@ -221,9 +222,9 @@ Job bwd_job(qsl_system* sys, const qsl_bwd_args* a, const WsLayout& L, char* ws,
     j.mode = a->mode;
     j.gw = gw;
     j.by_e = by_e ? 1 : 0;
-    // FP32: the walker order of the tiles, as the forward's (the dA by
-    // electron's groups and the tile kernels read it)
-    if (a->mode == QSL_FP32) j.wperm = (const int*)(ws + L.perm_off[s]);
+    // the walker order of the tiles, as the forward's (the dA by electron's
+    // groups and the tile kernels read it)
+    if (L.sorted) j.wperm = (const int*)(ws + L.perm_off[s]);
     j.W = a->W;
     j.R = a->R;
     j.nwin = (int*)(ws + L.nwin_off[s]);
@@ -784,17 +785,16 @@ const char* contract_label(int mode) {
 // a small population leaves most of the chip idle, and two launches in a row
 // take twice one's latency (two spins of 22 electrons, 64 walkers: 138 us one
 // spin after the other).
-static qsl_status forward_enqueue(qsl_system* sys, const qsl_fwd_args* a, char* ws, hipStream_t st) {
+static qsl_status forward_enqueue(qsl_system* sys, const qsl_fwd_args* a, const WsLayout& L, char* ws, hipStream_t st) {
     enum { SORT, SCREEN, CONTRACT, GJ0, GJ1, EPILOGUE };
-    const WsLayout L = ws_layout(sys->d, a->W, 1, a->mode, false);  // the forward's part only
     hipError_t e;
     if (a->status && (e = fill_u32(a->status, 0u, a->W, st)) != hipSuccess) return hip_fail(e, "status clear");
     CallLists P(ws + L.call_off);
     const int nmax = std::max(sys->d.n_up, sys->d.n_dn);
     int variant[2] = {-1, -1};
     for (int s = 0; s < 2; ++s) {
-        // FP32: each electron index's walkers in space-filling-curve order,
-        // so the tiles' survivor unions are tighter
+        // each electron index's walkers in space-filling-curve order, so the
+        // tiles' survivor unions are tighter
         Job j = fwd_job(sys, a, L, ws, s, /*sorted=*/true);
         if (!j.n) continue;
         if (j.mode == QSL_FP64) j.f32_tile = contract_f64_tile(nmax);
@@ -884,21 +884,24 @@ qsl_status qsl_forward(qsl_system* sys, const qsl_fwd_args* a, void* stream) {
     if (r != QSL_OK || a->W == 0) return r;
     WsLayout L = ws_layout(sys->d, a->W, 1, a->mode, false);
     if (!a->ws || a->ws_bytes < L.fwd_total) return bad(QSL_ERR_WORKSPACE, "workspace missing or too small");
-    return forward_enqueue(sys, a, (char*)a->ws, (hipStream_t)stream);
+    return forward_enqueue(sys, a, L, (char*)a->ws, (hipStream_t)stream);
 }
 
 qsl_status qsl_forward_noalloc(qsl_system* sys, const qsl_fwd_args* a, void* stream) {
     qsl_status r = forward_check(sys, a);
     if (r != QSL_OK || a->W == 0) return r;
-    const WsLayout L = ws_layout(sys->d, a->W, 1, a->mode, false);
-    if (L.fwd_total > (size_t)QSL_NOALLOC_SCRATCH_BYTES + CALL_LISTS_BYTES)
+    constexpr size_t LIMIT = (size_t)QSL_NOALLOC_SCRATCH_BYTES + CALL_LISTS_BYTES;
+    WsLayout L = ws_layout(sys->d, a->W, 1, a->mode, false);
+    // FP64 without the walker order, the same outputs, where that fits
+    if (L.fwd_total > LIMIT && a->mode == QSL_FP64) L = ws_layout(sys->d, a->W, 1, a->mode, false, /*sort=*/false);
+    if (L.fwd_total > LIMIT)
         return bad(QSL_ERR_WORKSPACE, "noalloc: the forward of this many walkers needs " + std::to_string(L.fwd_total) +
                                           " bytes of workspace, more than the " +
                                           std::to_string((size_t)QSL_NOALLOC_SCRATCH_BYTES) + " of the static scratch");
     void* ws = nullptr;
     if ((r = scratch_address(&ws)) != QSL_OK) return r;
     g_prof_suspend = true;
-    r = forward_enqueue(sys, a, (char*)ws, (hipStream_t)stream);
+    r = forward_enqueue(sys, a, L, (char*)ws, (hipStream_t)stream);
     g_prof_suspend = false;
     return r;
 }
@@ -944,9 +947,11 @@ qsl_status qsl_backward(qsl_system* sys, const qsl_bwd_args* a, void* stream) {
         P.job[s] = j;
         if (j.dA32 && (e = fill_u32((uint32_t*)j.dA32, 0u, (int64_t)j.n * d.n_basis, st)) != hipSuccess)
             return hip_fail(e, "dA accumulator clear");
-        if (j.wperm) P.add(SORT, s, wsort_blocks(j));  // the walker order of the tiles (as the forward's)
         const bool dA = a->dA[s] != nullptr;
-        if ((a->dR && !a->drift) || (dA && by_e)) P.add(SCREEN, s, screen_blocks(j, 0));  // the tile lists
+        if ((a->dR && !a->drift) || (dA && by_e)) {
+            if (j.wperm) P.add(SORT, s, wsort_blocks(j));  // the walker order of the tiles (as the forward's)
+            P.add(SCREEN, s, screen_blocks(j, 0));         // the tile lists
+        }
         if (a->dR && a->drift) {
             P.add(DR, s, dr_drift_blocks(j));
         } else if (a->dR) {

@@ -131,7 +131,8 @@ static qsl_status prepare(qsl_plan* p, hipStream_t st) {
     size_t total = 256;  // the item counter
     for (int i = 0; i < p->n_sys; ++i) {
         p->gw[i] = plan_gw(p, i);
-        p->lay[i] = ws_layout(p->sys[i]->d, p->W[i], p->gw[i], p->mode, plan_by_e(p, i));
+        p->lay[i] = ws_layout(p->sys[i]->d, p->W[i], p->gw[i], p->mode, plan_by_e(p, i),
+                              /*sort=*/p->mode == QSL_FP32 || p->tune.det_dA == 0);
         p->ws_off[i] = total;
         total = round_up(total + p->lay[i].total, 256);
     }

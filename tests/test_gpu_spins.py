@@ -59,3 +59,19 @@ def test_each_determinant_as_a_forward(n_up, n_dn, n_det, W):
         one = run_gpu_forward(T, R, "fp64")
         np.testing.assert_array_equal(out["det_logdet"][K].cpu().numpy(), one["logdet"])
         np.testing.assert_array_equal(out["det_sign"][K].cpu().numpy(), one["sign"])
+
+
+@pytest.mark.parametrize("W", [1985, 1986, 2100])
+def test_walker_order_changes_nothing(W):
+    """FP64: C and what follows from it, for the first walkers of a call whose
+    tiles take the walkers in an order of their own (from 65536 electrons on)
+    or not, are bit for bit those of a call of these walkers alone (one tile,
+    no order): the products are one chain over the slots, to which slots that
+    survive for other walkers add zeros."""
+    print(f"[case] walker order W={W}", flush=True)
+    sysm, A_up, A_dn = random_tiny(n_atoms=6, n_up=17, n_dn=16, seed=W)
+    R = walkers_near(sysm, W, seed=5)
+    S = make_gpu_system(sysm, A_up, A_dn)
+    all_, few = run_gpu_forward(S, R, "fp64"), run_gpu_forward(S, np.ascontiguousarray(R[:20]), "fp64")
+    for k in ("C_up", "C_dn", "Dinv_up", "Dinv_dn", "logdet", "sign", "drift", "lap", "status"):
+        np.testing.assert_array_equal(all_[k][:20], few[k])
