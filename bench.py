@@ -80,9 +80,11 @@ def work_per_step(sysm, nnz, W, mode, tile=2):
 
     def gsplit_bytes(D_read):
         return sum(((8.0 * n * n if D_read else 0.0) + 4.0 * -(-n // 32) * 32 * -(-n // 224) * 224) * W for n in ns)
-    # FP32 dA by electron: G = g D^-1 in FP32, rows of whole 224-MO blocks,
-    # written by the drift / Laplacian epilogue (D^-1 read once for both)
-    g32 = sum(4.0 * n * -(-n // 224) * 224 * W for n in ns) if mode == "fp32" else 0.0
+    # FP32 dA by electron: G = g D^-1 in FP32, rows of whole 32-MO blocks
+    # (224-MO blocks past 224), written by the drift / Laplacian epilogue
+    # (D^-1 read once for both)
+    g32_ld = [-(-n // 32) * 32 if n <= 224 else -(-n // 224) * 224 for n in ns]
+    g32 = sum(4.0 * n * ld * W for n, ld in zip(ns, g32_ld)) if mode == "fp32" else 0.0
     cpeak = PEAK["bf16x3"] if mode == "fp32" and tile == 2 else PEAK[mode]
     return {
         f"contract_{mode}": (contract, cpeak[0], cpeak[1], "TFLOP/s"),

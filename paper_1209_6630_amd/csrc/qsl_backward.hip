@@ -880,7 +880,7 @@ __device__ __forceinline__ void adj_dae_body(const Job& j, int bx, int by) {
             for (int ps = 0; ps < DE_GP / DE_THREADS; ++ps) {
                 const int p = ps * DE_THREADS + tid;
                 const int row = min(p / (DE_MB / 4), kw - 1), c = p % (DE_MB / 4);
-                const float* src = G32 + ((size_t)wl[row] * n + e) * ldg + i0 + 4 * c;
+                const float* src = G32 + ((size_t)wl[row] * n + e) * ldg + min(i0 + 4 * c, ldg - 4);
                 __builtin_amdgcn_global_load_lds((const void*)src,
                                                  (__attribute__((address_space(3))) void*)&G[(ps * DE_THREADS + wave * 64) * 4],
                                                  16, 0, 0);
@@ -900,10 +900,11 @@ __device__ __forceinline__ void adj_dae_body(const Job& j, int bx, int by) {
             __syncthreads();
             if (wave * 32 < cnt) {
                 const int h = lane >> 5, c = lane & 31;
-                // every MO block runs: G is zero past n, so blocks there add
-                // zeros (per-block branches kept the compiler from batching
-                // the operand reads).  The operands of k-step s + 1 are read
-                // before the MFMAs of k-step s.
+                // every MO block runs: G is zero past n (past its row, its last
+                // four again), and rows there are not flushed (per-block
+                // branches kept the compiler from batching the operand
+                // reads).  The operands of k-step s + 1 are read before the
+                // MFMAs of k-step s.
                 constexpr int NMB = DE_MB / 32;
                 float a[2][NMB], bv[2];
                 auto fetch = [&](int s2, int q) __attribute__((always_inline)) {
@@ -981,6 +982,7 @@ __device__ __forceinline__ void adj_dae_s3_body(const Job& j, int bx, int by) {
     const int nw = (int)min<int64_t>(gw, W - w0);
     const int i0 = by * DE_MB;
     const int ldg = g32_ld(n);
+    const int nmb = __builtin_amdgcn_readfirstlane((min(DE_MB, n - i0) + 31) >> 5);  // 32-MO blocks
     const int N = s.n_up + s.n_dn, eoff = spin ? s.n_up : 0;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1030,7 +1032,7 @@ __device__ __forceinline__ void adj_dae_s3_body(const Job& j, int bx, int by) {
 #pragma unroll
             for (int ps = 0; ps < DS_PASS; ++ps) {
                 const int u = ps * DE_THREADS + tid;
-                const int kp = u % (DE_KW / 2), mq = min(u / (DE_KW / 2), DE_MB / 4 - 1);
+                const int kp = u % (DE_KW / 2), mq = min(u / (DE_KW / 2), 8 * nmb - 1);
                 const int r0 = min(2 * kp, kw - 1), r1 = min(2 * kp + 1, kw - 1);
                 ga[ps] = *(const float4*)(G32 + ((size_t)wl[r0] * n + e) * ldg + i0 + 4 * mq);
                 gb[ps] = *(const float4*)(G32 + ((size_t)wl[r1] * n + e) * ldg + i0 + 4 * mq);
@@ -1048,8 +1050,12 @@ __device__ __forceinline__ void adj_dae_s3_body(const Job& j, int bx, int by) {
             }
             // the G planes: per unit and MO, one packed pair (walkers 2 kp,
             // 2 kp + 1) per plane; sixteen lanes fill one row's 64 bytes
+            // (blocks past n: the planes keep what they hold, for rows that are
+            // not flushed; leaving out their loads or products as well took
+            // 6.1 ms instead of 5.9 at 217 MOs for 0.56 instead of 0.60 at 79)
 #pragma unroll
             for (int ps = 0; ps < DS_PASS; ++ps) {
+                if (2 * ps >= nmb) break;  // 64 MOs a pass
                 const int u = ps * DE_THREADS + tid;
                 if (u < DS_UNITS) {
                     const int kp = u % (DE_KW / 2), mq = u / (DE_KW / 2);

@@ -180,17 +180,16 @@ __global__ __launch_bounds__(256) void epilogue_batched(const Job* jobs, const i
 int epilogue_blocks(const Job& j) { return (int)((j.W * j.n + 3) / 4); }
 
 // G = g D^-1 rounded to FP32 (0 where g = 0, and past n), [W][n][g32_ld(n)]:
-// the dA by electron's operand, for walkers bound without the epilogue.
+// the dA by electron's operand, for walkers bound without the epilogue.  One
+// wave per row.
 __device__ __forceinline__ void g32_body(const Job& j, int bx) {
     const int n = j.n, ld = g32_ld(n);
-    const int64_t q = (int64_t)bx * 256 + threadIdx.x;
-    if (q >= j.W * n * ld) return;
-    const int i = (int)(q % ld);
-    const int64_t we = q / ld;  // w * n + e
+    const int64_t we = (int64_t)bx * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // w * n + e
+    if (we >= j.W * n) return;
     const double gv = j.g[2 * (we / n) + j.spin];
-    float v = 0.f;
-    if (i < n && gv != 0.0) v = (float)(gv * gmem(j.Dinv)[we * n + i]);
-    gmem(j.g32)[q] = v;
+    const double* d = j.Dinv + we * n;
+    float* out = j.g32 + we * ld;
+    for (int i = threadIdx.x & 63; i < ld; i += 64) gmem(out)[i] = i < n && gv != 0.0 ? (float)(gv * gmem(d)[i]) : 0.f;
 }
 
 __global__ __launch_bounds__(256) void g32_kernel(Job j) { g32_body(j, blockIdx.x); }
@@ -199,7 +198,7 @@ __global__ __launch_bounds__(256) void g32_batched(const Job* jobs, const int* p
     batch_block(jobs, prefix, njobs, [&](const Job& j, int bx, int, int) { g32_body(j, bx); });
 }
 
-int g32_blocks(const Job& j) { return (int)((j.W * j.n * g32_ld(j.n) + 255) / 256); }
+int g32_blocks(const Job& j) { return (int)((j.W * j.n + 3) / 4); }
 
 hipError_t launch_g32(const Job& j, hipStream_t st) {
     if (!j.g32 || !j.n || !j.W) return hipSuccess;
