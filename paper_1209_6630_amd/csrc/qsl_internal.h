@@ -50,9 +50,8 @@ struct WinRec {
     double f64[WIN];
     double c64[WIN][QSL_PMAX];
 };
-// 16-byte pieces of a record read in FP32 / split-BF16 (prefix) or FP64 mode
+// 16-byte pieces of a record read in FP32 / split-BF16 (a prefix)
 constexpr int WINREC_Q32 = (int)(offsetof(WinRec, f64) / 16);
-constexpr int WINREC_Q64 = (int)(sizeof(WinRec) / 16);
 static_assert(offsetof(WinRec, f64) % 16 == 0 && sizeof(WinRec) % 16 == 0, "records are copied in 16-byte pieces");
 
 // Everything the AO evaluation of one slot needs (the FP32 contraction
@@ -422,21 +421,6 @@ __device__ __forceinline__ double readlane_f64(double x, int lane) {
     const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
     const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
     return __longlong_as_double(((uint64_t)hi << 32) | lo);
-}
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double x) {
-    const uint64_t u = __double_as_longlong(x);
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0u, (uint32_t)u, CTRL, 0xf, 0xf, false);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0u, (uint32_t)(u >> 32), CTRL, 0xf, 0xf, false);
-    return __longlong_as_double(((uint64_t)hi << 32) | lo);
-}
-
-template <int CTRL>
-__device__ __forceinline__ void argmax_step(double& best, int& bi) {
-    const double ob = dpp_f64<CTRL>(best);
-    const int oi = __builtin_amdgcn_update_dpp(0, bi, CTRL, 0xf, 0xf, false);
-    if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
 }
 
 // Timing of kernel launches with HIP events (enabled by qsl_profile_enable).
