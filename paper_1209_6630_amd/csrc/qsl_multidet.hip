@@ -158,6 +158,7 @@ __global__ void combine_kernel(MDComb c) {
 // matrix.
 constexpr size_t MD_GROUP_BYTES = (size_t)512 << 20;
 constexpr int64_t MD_GROUP_MATRICES = 65536;
+constexpr int MD_GROUP_MAX = 4096;  // (their Jobs: 19 MB)
 
 struct MDLayout {
     WsLayout base;
@@ -173,7 +174,7 @@ static MDLayout md_layout(const DevSys& d, const DevMO mo[2], int64_t W, int mod
     const int N = d.n_up + d.n_dn;
     size_t one = 0;  // bytes of a determinant
     for (int s = 0; s < 2; ++s) one += (size_t)W * n_spin(d, s) * n_spin(d, s) * (cb + 8);
-    int g = (int)std::min<size_t>({(size_t)n_det, MD_GROUP_BYTES / std::max<size_t>(one, 1),
+    int g = (int)std::min<size_t>({(size_t)std::min(n_det, MD_GROUP_MAX), MD_GROUP_BYTES / std::max<size_t>(one, 1),
                                    (size_t)(MD_GROUP_MATRICES / std::max<int64_t>(2 * W, 1))});
     if (g < 1 || gj_blocked(d.n_up) || gj_blocked(d.n_dn)) g = 1;
     L.group = (n_det + (n_det + g - 1) / g - 1) / ((n_det + g - 1) / g);  // groups of like sizes
