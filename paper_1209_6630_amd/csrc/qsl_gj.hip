@@ -100,6 +100,8 @@ struct GJShared {
     int xready;                // last panel handed over to the panel wave
     int xfree;                 // last panel whose columns were taken from there
     int bad;                   // 1: zero pivot, 2: non-finite pivot
+    int bad_panel;             // its panel (np: none so far)
+    int late;                  // a wave gave up waiting for the panel's columns to be taken back
     // (the panel first: its addresses are constants within an LDS
     // instruction's offset)
     __device__ double* X() { return main; }
@@ -397,7 +399,10 @@ __device__ __forceinline__ void gjt_panels(const GJArgs& j, GJShared<NT>& S, int
                 const int row = lane + 64 * r;
                 open[r] = __ballot(row < 16 * np && S.ord_of(row & 255) == 0);
             }
-            if (code && lane == 0) S.bad = code;
+            if (code && lane == 0) {
+                S.bad = code;
+                S.bad_panel = p;
+            }
         } else {
             // the panel's columns, for the wave that owns them
 #pragma unroll
@@ -529,7 +534,9 @@ __device__ __forceinline__ void gjt_update(const GJArgs& j, GJShared<NT>& S, int
 #pragma unroll 1
     for (int p = 0; p < np; ++p) {
         __syncthreads();  // F of panel p is published; every update of panel p - 1 is done
-        if (S.bad) return;
+        // (the panel wave may already be past panel p + 1: a pivot that fails
+        // there ends this loop for all waves at the next barrier alike)
+        if (S.bad_panel <= p) return;
         const double* Fp = S.F(p);
         const double* L = Fp + lg * LS + li;
         // the panel's columns come back as their own steps left them
@@ -620,7 +627,7 @@ __device__ __forceinline__ void gjt_update(const GJArgs& j, GJShared<NT>& S, int
                 }
             }
             if (pass == 0) {
-                flag_wait(&S.xfree, p);
+                if (!flag_wait(&S.xfree, p) && lane == 0) S.late = 1;
                 if (second) stage_tile(I1{}, p + 1);
                 else stage_tile(I0{}, p + 1);
                 __builtin_amdgcn_s_setprio(0);
@@ -628,6 +635,7 @@ __device__ __forceinline__ void gjt_update(const GJArgs& j, GJShared<NT>& S, int
         }
     }
     __syncthreads();  // the panels are no longer read
+    if (S.late) return;
     const uint4 o4 = *(const uint4*)S.ord[li];
     const uint32_t ov[4] = {o4.x, o4.y, o4.z, o4.w};
     auto step_of = [&](int ti) __attribute__((always_inline)) { return (int)((ov[ti >> 2] >> (8 * (ti & 3))) & 0xffu) - 1; };
@@ -672,23 +680,24 @@ __device__ __forceinline__ void gjt_body(const GJArgs& j, int w) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid < 64) ((uint32_t*)S.ord)[tid] = 0u;
-    if (tid == 0) { S.xready = S.xfree = -1; S.bad = 0; }
+    if (tid == 0) { S.xready = S.xfree = -1; S.bad = S.late = 0; S.bad_panel = (j.n + 15) >> 4; }
     __syncthreads();
     if (wave == P::NU) {
         gjt_panels<NT>(j, S, w, lane);
         if (!S.bad) {
             __syncthreads();
-            for (int q0 = 0; q0 < j.n; q0 += P::QC) gjt_copy_out<NT>(j, S, w, q0, wave, lane);
+            if (!S.late)
+                for (int q0 = 0; q0 < j.n; q0 += P::QC) gjt_copy_out<NT>(j, S, w, q0, wave, lane);
         }
     } else {
         gjt_update<NT>(j, S, w, wave, lane);
     }
-    if (S.bad) {
-        // undefined inverse: NaN, log|det| = -inf, sign = 0
+    if (S.bad || S.late) {
+        // undefined inverse: NaN, sign = 0, log|det| = -inf (a zero pivot) or NaN
         const size_t nn = (size_t)j.n * j.n;
         double* Dw = j.Dinv + (size_t)w * nn;
         for (size_t q = tid; q < nn; q += P::THREADS) Dw[q] = __longlong_as_double(0x7ff8000000000000ll);
-        if (tid == 0) {
+        if (tid == 64 * P::NU) {  // (the panel wave, which may have written a log|det|)
             if (j.logdet) j.logdet[2 * (size_t)w + j.spin] = S.bad == 1 ? -INFINITY : __longlong_as_double(0x7ff8000000000000ll);
             if (j.sign) j.sign[2 * (size_t)w + j.spin] = 0;
             if (j.status) atomicOr(j.status + w, S.bad == 1 ? QSL_STATUS_SINGULAR : QSL_STATUS_NONFINITE);
