@@ -158,14 +158,27 @@ __device__ __forceinline__ double gj_recip(double pv) {
 
 // A panel one of whose largest keys was no ordinary number's: its steps on
 // the panel in LDS, with NaN left out of the search.  Returns 0, or 1 where no
-// row or a zero is left, 2 where the pivot is infinite.
+// row or a zero is left, 2 where the pivot is infinite.  The identity's steps
+// past n are taken as they are known to be: the infinite reciprocal of a
+// subnormal pivot has left NaN in its rows by then (0 times infinity).
 template <int NT>
-__device__ __forceinline__ int gjt_panel_careful(GJShared<NT>& S, int p, int n16, int lane) {
+__device__ __forceinline__ int gjt_panel_careful(GJShared<NT>& S, int p, int n, int lane) {
     using P = GJT<NT>;
     constexpr int LS = P::LS;
+    const int n16 = (n + 15) & ~15;
     double *X = S.X(), *F = S.F(p);
 #pragma unroll 1
     for (int k = 0; k < 16; ++k) {
+        if (16 * p + k >= n) {
+            if (lane == 0) {
+                S.pvs[16 * p + k] = 1.0;
+                S.perm[16 * p + k] = 16 * p + k;
+                S.ord_of(16 * p + k) = (uint8_t)(16 * p + k + 1);
+            }
+#pragma unroll 1
+            for (int row = lane; row < P::NP; row += 64) F[k * LS + row] = 0.0;
+            continue;
+        }
         uint64_t best = 0;  // |x| and 255 - i, or the key, to be largest
         int at = 0;
 #pragma unroll 1
@@ -393,7 +406,7 @@ __device__ __forceinline__ void gjt_panels(const GJArgs& j, GJShared<NT>& S, int
             }
         });
         if (__builtin_expect(odd || code, 0)) {
-            if (!code) code = gjt_panel_careful<NT>(S, p, 16 * np, lane);
+            if (!code) code = gjt_panel_careful<NT>(S, p, n, lane);
 #pragma unroll
             for (int r = 0; r < RPL; ++r) {
                 const int row = lane + 64 * r;
