@@ -166,7 +166,8 @@ struct MDLayout {
     size_t corb[2], c1[2], dinv[2], list[4], logdet, sign, drift, lap, dstatus, st0, occ, coef, total;
 };
 
-static MDLayout md_layout(const DevSys& d, const DevMO mo[2], int64_t W, int mode, int n_det) {
+// (group_max: at most so many determinants per group)
+static MDLayout md_layout(const DevSys& d, const DevMO mo[2], int64_t W, int mode, int n_det, int group_max = MD_GROUP_MAX) {
     MDLayout L{};
     L.base = ws_layout(d, W, 1, mode, false, /*sort=*/false);  // the forward's part
     size_t off = L.base.fwd_total;
@@ -174,7 +175,7 @@ static MDLayout md_layout(const DevSys& d, const DevMO mo[2], int64_t W, int mod
     const int N = d.n_up + d.n_dn;
     size_t one = 0;  // bytes of a determinant
     for (int s = 0; s < 2; ++s) one += (size_t)W * n_spin(d, s) * n_spin(d, s) * (cb + 8);
-    int g = (int)std::min<size_t>({(size_t)std::min(n_det, MD_GROUP_MAX), MD_GROUP_BYTES / std::max<size_t>(one, 1),
+    int g = (int)std::min<size_t>({(size_t)std::min(n_det, group_max), MD_GROUP_BYTES / std::max<size_t>(one, 1),
                                    (size_t)(MD_GROUP_MATRICES / std::max<int64_t>(2 * W, 1))});
     if (g < 1 || gj_blocked(d.n_up) || gj_blocked(d.n_dn)) g = 1;
     L.group = (n_det + (n_det + g - 1) / g - 1) / ((n_det + g - 1) / g);  // groups of like sizes
@@ -249,7 +250,11 @@ qsl_status qsl_multidet_forward(qsl_system* sys, const qsl_multidet_args* a, voi
     }
     if (a->W == 0) return QSL_OK;
     if (!a->R) return bad(QSL_ERR_INVALID_ARG, "NULL R");
-    const MDLayout L = md_layout(d, sys->mo, a->W, a->mode, a->n_det);
+    // A workspace sized for more walkers or determinants always serves fewer:
+    // its groups may have been smaller, then these are too (one determinant at
+    // a time needs less for less of either).
+    MDLayout L = md_layout(d, sys->mo, a->W, a->mode, a->n_det);
+    for (int g = L.group - 1; a->ws_bytes < L.total && g >= 1; --g) L = md_layout(d, sys->mo, a->W, a->mode, a->n_det, g);
     if (!a->ws || a->ws_bytes < L.total) return bad(QSL_ERR_WORKSPACE, "workspace missing or too small");
     hipStream_t st = (hipStream_t)stream;
     char* ws = (char*)a->ws;

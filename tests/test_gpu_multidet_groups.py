@@ -57,3 +57,38 @@ def test_groups(n_up, n_dn, W, n_det):
         want = (w[:, :, None] * x).sum(0)
         bound = 2e-13 * (1 + amp)[:, None] * (np.abs(w)[:, :, None] * np.abs(x)).sum(0) + 1e-300
         assert np.all(np.abs(got[k].reshape(W, -1) - want) <= bound), k
+
+
+@pytest.mark.parametrize("W_ws,nd_ws,W,n_det", [(17000, 2, 16384, 2), (33000, 4, 9000, 3)])
+def test_workspace_of_a_larger_call(W_ws, nd_ws, W, n_det):
+    """A workspace sized for more walkers (whose groups are smaller, so that
+    it may hold less) serves fewer, with the same outputs; one byte less than
+    a single determinant at a time needs is refused."""
+    import ctypes as ct
+    import torch
+    from paper_1209_6630_amd._lib import MultidetArgs, lib
+    print(f"[case] determinants' workspace {W_ws}x{nd_ws} for {W}x{n_det}", flush=True)
+    sysm, A_up, A_dn = random_tiny(n_atoms=5, n_up=10, n_dn=9, seed=4)
+    S = make_gpu_system(sysm, A_up, A_dn)
+    R = torch.from_numpy(walkers_near(sysm, W, seed=2)).cuda()
+    occ = np.array([np.concatenate([np.roll(np.arange(10), K), np.arange(9)]) for K in range(n_det)], np.int32)
+    coef = np.linspace(1.0, 2.0, n_det)
+    want = S.multidet_forward(R, occ, coef, "fp64")
+    n = ct.c_size_t()
+    assert lib().qsl_multidet_workspace_size(S._h, W_ws, 0, nd_ws, ct.byref(n)) == 0
+    got = {k: torch.zeros_like(v) for k, v in want.items() if not k.startswith("_")}
+    ws = torch.empty(n.value, dtype=torch.uint8, device="cuda")
+
+    def call(ws_bytes):
+        a = MultidetArgs(W, R.data_ptr(), 0, n_det, occ.ctypes.data_as(ct.POINTER(ct.c_int32)),
+                         coef.ctypes.data_as(ct.POINTER(ct.c_double)), got["logpsi"].data_ptr(), got["sign"].data_ptr(),
+                         got["drift"].data_ptr(), got["lap"].data_ptr(), got["status"].data_ptr(),
+                         got["det_logdet"].data_ptr(), got["det_sign"].data_ptr(), ws.data_ptr(), ws_bytes)
+        return lib().qsl_multidet_forward(S._h, ct.byref(a), ct.c_void_p(torch.cuda.current_stream().cuda_stream))
+
+    assert call(ws.numel()) == 0
+    torch.cuda.synchronize()
+    for k, v in got.items():
+        np.testing.assert_array_equal(v.cpu().numpy(), want[k].cpu().numpy(), err_msg=k)
+    assert lib().qsl_multidet_workspace_size(S._h, W, 0, 1, ct.byref(n)) == 0
+    assert call(n.value - 1) == 4
