@@ -784,11 +784,10 @@ const char* contract_label(int mode) {
 // ws_layout); enqueues kernels only.  Both spins share one launch per phase:
 // a small population leaves most of the chip idle, and two launches in a row
 // take twice one's latency (two spins of 22 electrons, 64 walkers: 138 us one
-// spin after the other).
-static qsl_status forward_enqueue(qsl_system* sys, const qsl_fwd_args* a, const WsLayout& L, char* ws, hipStream_t st) {
+// spin after the other).  spins: bit s set where spin s takes part.
+static qsl_status forward_spins(qsl_system* sys, const qsl_fwd_args* a, const WsLayout& L, char* ws, hipStream_t st, int spins) {
     enum { SORT, SCREEN, CONTRACT, GJ0, GJ1, EPILOGUE };
     hipError_t e;
-    if (a->status && (e = fill_u32(a->status, 0u, a->W, st)) != hipSuccess) return hip_fail(e, "status clear");
     CallLists P(ws + L.call_off);
     const int nmax = std::max(sys->d.n_up, sys->d.n_dn);
     int variant[2] = {-1, -1};
@@ -796,7 +795,7 @@ static qsl_status forward_enqueue(qsl_system* sys, const qsl_fwd_args* a, const 
         // each electron index's walkers in space-filling-curve order, so the
         // tiles' survivor unions are tighter
         Job j = fwd_job(sys, a, L, ws, s, /*sorted=*/true);
-        if (!j.n) continue;
+        if (!j.n || !(spins >> s & 1)) continue;
         if (j.mode == QSL_FP64) j.f32_tile = contract_f64_tile(nmax);
         P.job[s] = j;
         if (j.wperm) P.add(SORT, s, wsort_blocks(j));
@@ -822,7 +821,7 @@ static qsl_status forward_enqueue(qsl_system* sys, const qsl_fwd_args* a, const 
     }
     if (P.any(CONTRACT)) {
         ProfScope ps(contract_label(a->mode), st);
-        const int tile = P.job[sys->d.n_up ? 0 : 1].f32_tile;
+        const int tile = P.job[variant[0] >= 0 ? 0 : 1].f32_tile;
         e = P.run(CONTRACT, [&](const Job* js, const int* pre, int nj, int nb) {
             return launch_contract_batched(a->mode, tile, nullptr, js, pre, nj, nb, st);
         });
@@ -839,7 +838,7 @@ static qsl_status forward_enqueue(qsl_system* sys, const qsl_fwd_args* a, const 
         if (e != hipSuccess) return hip_fail(e, "inversion kernel");
     }
     for (int s = 0; s < 2; ++s)  // a spin without electrons: log|det| = 0, sign = +1
-        if (!n_spin(sys->d, s) && (e = launch_gj(fwd_job(sys, a, L, ws, s), st)) != hipSuccess)
+        if ((spins >> s & 1) && !n_spin(sys->d, s) && (e = launch_gj(fwd_job(sys, a, L, ws, s), st)) != hipSuccess)
             return hip_fail(e, "empty spin kernel");
     if (P.any(EPILOGUE)) {
         ProfScope ps("drift_lap", st);
@@ -847,6 +846,28 @@ static qsl_status forward_enqueue(qsl_system* sys, const qsl_fwd_args* a, const 
         if (e != hipSuccess) return hip_fail(e, "epilogue kernel");
     }
     return QSL_OK;
+}
+
+// Both spins together, unless one's C or D^-1 shares memory with the other's (a
+// caller that needs neither may give one buffer for both spins): then one spin
+// after the other, as each reads its own C and D^-1 to the end.
+static qsl_status forward_enqueue(qsl_system* sys, const qsl_fwd_args* a, const WsLayout& L, char* ws, hipStream_t st) {
+    hipError_t e;
+    if (a->status && (e = fill_u32(a->status, 0u, a->W, st)) != hipSuccess) return hip_fail(e, "status clear");
+    uintptr_t at[2][2], end[2][2];
+    for (int s = 0; s < 2; ++s) {
+        const size_t nn = (size_t)a->W * n_spin(sys->d, s) * n_spin(sys->d, s);
+        at[s][0] = (uintptr_t)a->C[s];
+        end[s][0] = at[s][0] + nn * 5 * (a->mode == QSL_FP64 ? 8 : 4);
+        at[s][1] = (uintptr_t)a->Dinv[s];
+        end[s][1] = at[s][1] + nn * 8;
+    }
+    bool shared = false;
+    for (int x = 0; x < 2; ++x)
+        for (int y = 0; y < 2; ++y) shared |= at[0][x] < end[1][y] && at[1][y] < end[0][x];
+    if (!shared) return forward_spins(sys, a, L, ws, st, 3);
+    const qsl_status r = forward_spins(sys, a, L, ws, st, 1);
+    return r != QSL_OK ? r : forward_spins(sys, a, L, ws, st, 2);
 }
 
 // Workspace of qsl_forward_noalloc: a file-scope device array, one copy per
