@@ -1286,7 +1286,10 @@ __device__ __forceinline__ void adj_daf_body(const Job& j, int bx, int by) {
             int nbas = __builtin_amdgcn_readfirstlane(s.n_basis), lim = mine - lg;  // rows di < lim of lane row lg exist
             asm volatile("" : "+s"(nbas));
             asm volatile("" : "+v"(lim));
-            double* col = j.dA64 + (size_t)(i0 + lg) * nbas + max(ao, 0);
+            // (partial sums: one per electron, zero before, this workgroup the
+            // only one to add to these entries)
+            double* to = j.dApart ? (double*)j.dApart + (size_t)e * n * nbas : j.dA64;
+            double* col = to + (size_t)(i0 + lg) * nbas + max(ao, 0);
 #pragma unroll
             for (int t = 0; t < DF_MT; ++t)
 #pragma unroll

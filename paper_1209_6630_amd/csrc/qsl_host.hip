@@ -119,20 +119,32 @@ ProfScope::~ProfScope() {
 }
 
 
-// Walkers per dA group: they share one window list (screened together).
-// Default walkers per dA group: by electron, the groups are long (the
-// flush is one atomic per dA entry and group); by 32-electron range, the
-// group's window union stays small.
-int bw_group(int64_t W, bool by_e) { return (int)std::min<int64_t>(W, by_e ? 1024 : 128); }
+// The form of a spin's dA, and its walkers per group (group: a plan's
+// adj_group, or 0).  By default, by electron, the groups are long (the flush is
+// one atomic per dA entry and group); by 32-electron range, the group's window
+// union stays small.
+// FP64 calls of one range (n <= 32) and one group of it have one writer per dA
+// entry by range, so that they give the same bits every time.  By electron
+// they keep that by partial sums (22 electrons a spin, 128 walkers: by range
+// 1910 us, by electron 65 with atomics), as long as those are small.
+DaRoute dA_route(const DevSys& d, int n, int64_t W, int mode, bool det, int group) {
+    const auto gw = [&](int most) { return (int)std::min<int64_t>(std::max<int64_t>(W, 1), group > 0 ? group : most); };
+    if (mode == QSL_BF16X3 || det || d.n_win > UNION_MAXWIN) return {DA_RANGE, gw(128)};
+    if (mode == QSL_FP64 && n <= TE && W <= gw(128))
+        return (size_t)n * n * d.n_basis * sizeof(double) <= DA_PARTS_BYTES ? DaRoute{DA_PARTS, gw(1024)} : DaRoute{DA_RANGE, gw(128)};
+    return {DA_ELECTRON, gw(1024)};
+}
 
 // Workspace layout.  The forward's regions come first: per spin,
 // tile_nwin[T_s] and tile_win[T_s][n_win], and the FP64 copy of the blocked
-// inversion; then the adjoint's: the lists per walker group of gw walkers
-// (windows per 32-electron range, or slots per electron with by_e), the
-// FP32 dA accumulator and the split-BF16 G.  A forward-only workspace ends
-// at fwd_total.
-WsLayout ws_layout(const DevSys& d, int64_t W, int gw, int mode, bool by_e, bool sort) {
+// inversion; then the adjoint's: the lists per walker group (windows per
+// 32-electron range, or slots per electron), the FP32 dA accumulator, the
+// split-BF16 G and the electrons' partial sums of dA (there also for more
+// walkers than use them, so that a workspace for more serves fewer).  A
+// forward-only workspace ends at fwd_total.
+WsLayout ws_layout(const DevSys& d, int64_t W, int mode, bool sort, bool det, int group) {
     WsLayout L{};
+    for (int s = 0; s < 2; ++s) L.da[s] = dA_route(d, n_spin(d, s), W, mode, det, group);
     size_t off = 0;
     L.job_off = off;
     off += JOBSLOT_BYTES;
@@ -158,8 +170,9 @@ WsLayout ws_layout(const DevSys& d, int64_t W, int gw, int mode, bool by_e, bool
     off += CALL_LISTS_BYTES;
     L.fwd_total = std::max<size_t>(off, 256);
     for (int s = 0; s < 2; ++s) {
-        int n = n_spin(d, s);
-        const size_t ngw = (size_t)((W + gw - 1) / std::max(gw, 1));
+        const int n = n_spin(d, s), gw = L.da[s].gw;
+        const bool by_e = L.da[s].by_e();
+        const size_t ngw = (size_t)((W + gw - 1) / gw);
         size_t groups = n ? (by_e ? (size_t)n : (size_t)tiles_per_walker(n)) * ngw : 0;
         const size_t cap = by_e ? (size_t)WIN * d.n_win : (size_t)d.n_win;
         L.gnwin_off[s] = off;
@@ -179,7 +192,13 @@ WsLayout ws_layout(const DevSys& d, int64_t W, int gw, int mode, bool by_e, bool
     for (int s = 0; s < 2; ++s) {
         const int n = n_spin(d, s);
         L.g32_off[s] = off;
-        if (by_e && mode == QSL_FP32 && n) off = round_up(off + (size_t)W * n * g32_ld(n) * sizeof(float), 256);
+        if (L.da[s].by_e() && mode == QSL_FP32 && n) off = round_up(off + (size_t)W * n * g32_ld(n) * sizeof(float), 256);
+    }
+    for (int s = 0; s < 2; ++s) {
+        const int n = n_spin(d, s);
+        const size_t bytes = (size_t)n * n * d.n_basis * sizeof(double);
+        L.part_off[s] = off;
+        if (mode == QSL_FP64 && n <= TE && bytes <= DA_PARTS_BYTES) off = round_up(off + bytes, 256);
     }
     L.total = std::max<size_t>(off, 256);
     return L;
@@ -213,14 +232,15 @@ Job fwd_job(qsl_system* sys, const qsl_fwd_args* a, const WsLayout& L, char* ws,
 }
 
 // The Job of one spin of an adjoint call.
-Job bwd_job(qsl_system* sys, const qsl_bwd_args* a, const WsLayout& L, char* ws, int s, int gw, bool by_e) {
+Job bwd_job(qsl_system* sys, const qsl_bwd_args* a, const WsLayout& L, char* ws, int s) {
+    const bool by_e = L.da[s].by_e();
     Job j{};
     j.s = sys->d;
     j.mo = sys->mo[s];
     j.spin = s;
     j.n = n_spin(sys->d, s);
     j.mode = a->mode;
-    j.gw = gw;
+    j.gw = L.da[s].gw;
     j.by_e = by_e ? 1 : 0;
     // the walker order of the tiles, as the forward's (the dA by electron's
     // groups and the tile kernels read it)
@@ -240,6 +260,7 @@ Job bwd_job(qsl_system* sys, const qsl_bwd_args* a, const WsLayout& L, char* ws,
         else j.dA32 = (float*)(ws + L.dA32_off[s]);
         if (a->mode == QSL_BF16X3) j.gsplit = (uint16_t*)(ws + L.gs_off[s]);
         if (by_e && a->mode == QSL_FP32) j.g32 = (float*)(ws + L.g32_off[s]);
+        if (L.da[s].form == DA_PARTS) j.dApart = ws + L.part_off[s];
     }
     j.f32_tile = F32_TILE_DEFAULT;
     return j;
@@ -713,8 +734,7 @@ qsl_status qsl_workspace_size(const qsl_system* sys, int64_t W, int32_t mode, in
     if (W < 0) return bad(QSL_ERR_INVALID_ARG, "W < 0");
     if (mode < QSL_FP64 || mode > QSL_BF16X3) return bad(QSL_ERR_INVALID_ARG, "bad mode");
     if (what < QSL_WS_FORWARD || what > QSL_WS_BOTH) return bad(QSL_ERR_INVALID_ARG, "bad workspace selector");
-    const bool by_e = dA_by_electron(mode, false) && sys->d.n_win <= UNION_MAXWIN;
-    const WsLayout L = ws_layout(sys->d, W, bw_group(W, by_e), mode, by_e);
+    const WsLayout L = ws_layout(sys->d, W, mode);
     *bytes = (what & QSL_WS_BACKWARD) ? L.total : L.fwd_total;
     return QSL_OK;
 }
@@ -903,7 +923,7 @@ extern "C" {
 qsl_status qsl_forward(qsl_system* sys, const qsl_fwd_args* a, void* stream) {
     qsl_status r = forward_check(sys, a);
     if (r != QSL_OK || a->W == 0) return r;
-    WsLayout L = ws_layout(sys->d, a->W, 1, a->mode, false);
+    WsLayout L = ws_layout(sys->d, a->W, a->mode);
     if (!a->ws || a->ws_bytes < L.fwd_total) return bad(QSL_ERR_WORKSPACE, "workspace missing or too small");
     return forward_enqueue(sys, a, L, (char*)a->ws, (hipStream_t)stream);
 }
@@ -912,9 +932,9 @@ qsl_status qsl_forward_noalloc(qsl_system* sys, const qsl_fwd_args* a, void* str
     qsl_status r = forward_check(sys, a);
     if (r != QSL_OK || a->W == 0) return r;
     constexpr size_t LIMIT = (size_t)QSL_NOALLOC_SCRATCH_BYTES + CALL_LISTS_BYTES;
-    WsLayout L = ws_layout(sys->d, a->W, 1, a->mode, false);
+    WsLayout L = ws_layout(sys->d, a->W, a->mode);
     // FP64 without the walker order, the same outputs, where that fits
-    if (L.fwd_total > LIMIT && a->mode == QSL_FP64) L = ws_layout(sys->d, a->W, 1, a->mode, false, /*sort=*/false);
+    if (L.fwd_total > LIMIT && a->mode == QSL_FP64) L = ws_layout(sys->d, a->W, a->mode, /*sort=*/false);
     if (L.fwd_total > LIMIT)
         return bad(QSL_ERR_WORKSPACE, "noalloc: the forward of this many walkers needs " + std::to_string(L.fwd_total) +
                                           " bytes of workspace, more than the " +
@@ -935,9 +955,14 @@ qsl_status qsl_backward(qsl_system* sys, const qsl_bwd_args* a, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
     const int N = d.n_up + d.n_dn;
+    const WsLayout L = ws_layout(d, a->W, a->mode);
+    // the spins' partial sums are written to dA whole, unless both are to add to one
+    const auto dA_bytes = [&](int s) { return (uintptr_t)n_spin(d, s) * d.n_basis * sizeof(double); };
+    const bool dA_apart = (uintptr_t)a->dA[0] + dA_bytes(0) <= (uintptr_t)a->dA[1] || (uintptr_t)a->dA[1] + dA_bytes(1) <= (uintptr_t)a->dA[0];
+    const auto whole = [&](int s) { return a->W && L.da[s].form == DA_PARTS && !a->accumulate_dA && dA_apart; };
     for (int s = 0; s < 2; ++s) {
         // FP64 accumulates into dA directly; with no walkers, dA = 0 in every mode
-        if (a->dA[s] && !a->accumulate_dA && n_spin(d, s) && (a->mode == QSL_FP64 || a->W == 0)) {
+        if (a->dA[s] && !a->accumulate_dA && n_spin(d, s) && (a->mode == QSL_FP64 || a->W == 0) && !whole(s)) {
             if ((e = fill_f64(a->dA[s], 0.0, (int64_t)n_spin(d, s) * d.n_basis, st)) != hipSuccess)
                 return hip_fail(e, "dA clear");
         }
@@ -951,20 +976,18 @@ qsl_status qsl_backward(qsl_system* sys, const qsl_bwd_args* a, void* stream) {
             return bad(QSL_ERR_SHAPE, "the MO set of a spin has more rows than electrons (qsl_set_orbitals)");
         if (!a->Dinv[s]) return bad(QSL_ERR_INVALID_ARG, "NULL Dinv");
     }
-    const bool by_e = dA_by_electron(a->mode, false) && d.n_win <= UNION_MAXWIN;
-    const int gw = bw_group(a->W, by_e);
-    WsLayout L = ws_layout(d, a->W, gw, a->mode, by_e);
     if (!a->ws || a->ws_bytes < L.total) return bad(QSL_ERR_WORKSPACE, "workspace missing or too small");
     char* ws = (char*)a->ws;
     // with the drift, dR is written whole (every electron of both spins)
     if (a->dR && !a->drift && (e = fill_f64(a->dR, 0.0, a->W * N * 3, st)) != hipSuccess)
         return hip_fail(e, "dR clear");
     // both spins in one launch per phase, as the forward
-    enum { SORT, SCREEN, DR, ADJ_H, GROUP, G, DA };
+    enum { SORT, SCREEN, DR, ADJ_H, SLOTS, G, DA_E, GROUP, DA_R };
     CallLists P(ws + L.call_off);
     for (int s = 0; s < 2; ++s) {
-        Job j = bwd_job(sys, a, L, ws, s, gw, by_e);
+        Job j = bwd_job(sys, a, L, ws, s);
         if (!j.n) continue;
+        const bool by_e = j.by_e != 0;
         P.job[s] = j;
         if (j.dA32 && (e = fill_u32((uint32_t*)j.dA32, 0u, (int64_t)j.n * d.n_basis, st)) != hipSuccess)
             return hip_fail(e, "dA accumulator clear");
@@ -983,15 +1006,24 @@ qsl_status qsl_backward(qsl_system* sys, const qsl_bwd_args* a, void* stream) {
         if (!dA) continue;
         // the slot lists of the (electron, walker group) pairs, or the window
         // lists of the groups
-        P.add(GROUP, s, by_e ? group_slots_blocks(j) : screen_blocks(j, 1));
+        P.add(by_e ? SLOTS : GROUP, s, by_e ? group_slots_blocks(j) : screen_blocks(j, 1));
         if (j.g32) P.add(G, s, g32_blocks(j));
         else if (j.gsplit) P.add(G, s, gsplit_blocks(j));
         Job t = j;
         if (by_e) adj_dae_grid(t);
         else adj_da_grid(t);
-        P.add(DA, s, t.gx, t.gy, t.gz);
+        P.add(by_e ? DA_E : DA_R, s, t.gx, t.gy, t.gz);
     }
     if ((e = P.store(st)) != hipSuccess) return hip_fail(e, "job lists");
+    {  // the spins' partial sums lie side by side
+        char *lo = nullptr, *hi = nullptr;
+        for (const Job& j : P.job) {
+            if (!j.dApart) continue;
+            if (!lo) lo = (char*)j.dApart;
+            hi = (char*)j.dApart + (size_t)j.n * j.n * d.n_basis * sizeof(double);
+        }
+        if ((e = fill_u32((uint32_t*)lo, 0u, (hi - lo) / 4, st)) != hipSuccess) return hip_fail(e, "dA partial sums clear");
+    }
     if (P.any(SORT)) {
         ProfScope ps("walker_order", st);
         e = P.run(SORT, [&](const Job* js, const int* pre, int nj, int nb) { return launch_wsort_batched(js, pre, nj, nb, st); });
@@ -1012,28 +1044,42 @@ qsl_status qsl_backward(qsl_system* sys, const qsl_bwd_args* a, void* stream) {
         e = P.run(ADJ_H, [&](const Job* js, const int* pre, int nj, int nb) { return launch_adj_h_batched(a->mode, js, pre, nj, nb, st); });
         if (e != hipSuccess) return hip_fail(e, "adjoint H kernel");
     }
+    if (P.any(SLOTS)) {
+        ProfScope ps("screen_group", st);
+        e = P.run(SLOTS, [&](const Job* js, const int* pre, int nj, int nb) { return launch_group_slots_batched(js, pre, nj, nb, st); });
+        if (e != hipSuccess) return hip_fail(e, "group slot kernel");
+    }
     if (P.any(GROUP)) {
         ProfScope ps("screen_group", st);
-        e = P.run(GROUP, [&](const Job* js, const int* pre, int nj, int nb) {
-            return by_e ? launch_group_slots_batched(js, pre, nj, nb, st) : launch_screen_batched(js, pre, nj, nb, 1, st);
-        });
-        if (e != hipSuccess) return hip_fail(e, by_e ? "group slot kernel" : "group screen kernel");
+        e = P.run(GROUP, [&](const Job* js, const int* pre, int nj, int nb) { return launch_screen_batched(js, pre, nj, nb, 1, st); });
+        if (e != hipSuccess) return hip_fail(e, "group screen kernel");
     }
     if (P.any(G)) {
-        ProfScope ps(by_e ? "g32" : "g_split", st);
+        const bool split = a->mode == QSL_BF16X3;
+        ProfScope ps(split ? "g_split" : "g32", st);
         e = P.run(G, [&](const Job* js, const int* pre, int nj, int nb) {
-            return by_e ? launch_g32_batched(js, pre, nj, nb, st) : launch_gsplit_batched(js, pre, nj, nb, st);
+            return split ? launch_gsplit_batched(js, pre, nj, nb, st) : launch_g32_batched(js, pre, nj, nb, st);
         });
-        if (e != hipSuccess) return hip_fail(e, by_e ? "G kernel" : "G split kernel");
+        if (e != hipSuccess) return hip_fail(e, split ? "G split kernel" : "G kernel");
     }
-    if (P.any(DA)) {
+    for (int ph : {DA_E, DA_R}) {
+        if (!P.any(ph)) continue;
         ProfScope ps("adjoint_dA", st);
-        e = P.run(DA, [&](const Job* js, const int* pre, int nj, int nb) {
-            return by_e ? launch_adj_dae_batched(a->mode, F32_TILE_DEFAULT, js, pre, nj, nb, st)
-                        : launch_adj_da_batched(a->mode, js, pre, nj, nb, st);
+        e = P.run(ph, [&](const Job* js, const int* pre, int nj, int nb) {
+            return ph == DA_E ? launch_adj_dae_batched(a->mode, F32_TILE_DEFAULT, js, pre, nj, nb, st)
+                              : launch_adj_da_batched(a->mode, js, pre, nj, nb, st);
         });
         if (e != hipSuccess) return hip_fail(e, "adjoint dA kernel");
     }
+    ReduceDA r[3] = {};
+    int nr = 0;
+    for (int s = 0; s < 2; ++s) {
+        const Job& j = P.job[s];
+        if (j.dApart) r[nr++] = ReduceDA{j.dApart, j.dA64, (int64_t)j.n * d.n_basis, dA_parts(j), whole(s) ? 0 : 2};
+    }
+    // (one after the other where both add to one dA)
+    if (!dA_apart && nr == 2 && (e = launch_reduce_dA(true, r[--nr], r[2], st)) != hipSuccess) return hip_fail(e, "dA reduction");
+    if (nr && (e = launch_reduce_dA(true, r[0], nr == 2 ? r[1] : r[2], st)) != hipSuccess) return hip_fail(e, "dA reduction");
     for (int s = 0; s < 2; ++s)
         if (P.job[s].dA32 && (e = launch_finalize_dA(P.job[s].dA32, a->dA[s], (int64_t)P.job[s].n * d.n_basis,
                                                      a->accumulate_dA, st)) != hipSuccess)

@@ -347,6 +347,7 @@ struct Job {
     // for all ranges, atomic flush), each walker group adding its block into
     // its own partial sum dApart[wb][n][N_b] (float, or double in FP64) with
     // plain loads and stores; the partials are reduced in a fixed order.
+    // With by_e (DA_PARTS): dApart[e][n][N_b], one per electron.
     void* dApart;
     int t_fix = -1;
     // dA by electron index: gnwin / gwin hold, per (electron, walker group
@@ -368,6 +369,8 @@ struct Job {
     int c_ld;
     int gx, gy, gz;          // the Job's grid in the current phase
 };
+// Partial sums of a Job with dApart.
+inline int dA_parts(const Job& j) { return j.by_e ? j.n : (int)((j.W + j.gw - 1) / j.gw); }
 __host__ __device__ inline int64_t c1_stride(const Job& j) { return j.c1_stride ? j.c1_stride : 5 * (int64_t)j.n * j.n; }
 // Bytes of the device Job copy of a per-system launch (Job, then two ints).
 constexpr size_t JOBSLOT_BYTES = (sizeof(Job) + 2 * sizeof(int) + 255) / 256 * 256;
@@ -438,13 +441,18 @@ qsl_status bad(qsl_status code, const std::string& msg);
 size_t round_up(size_t x, size_t a);
 hipError_t fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st);
 hipError_t fill_f64(double* p, double v, int64_t n, hipStream_t st);
-// Default walkers per dA group: they share one window list.
-int bw_group(int64_t W, bool by_e);
-// The adjoint's dA runs by electron index (walker groups of one electron,
-// an exact slot list per group, walkers as the contraction dimension) in
-// FP32 and FP64 unless the deterministic reduction is asked for; by
-// 32-electron ranges otherwise.
-inline bool dA_by_electron(int mode, bool det) { return mode != QSL_BF16X3 && !det; }
+// How a spin's dA is summed, and the walkers per group: by 32-electron range
+// (a group shares one window list), by electron index (walker groups of one
+// electron, an exact slot list per group, walkers as the contraction
+// dimension), each adding to dA with atomics, or by electron into partial sums
+// that are added in order.
+enum { DA_RANGE, DA_ELECTRON, DA_PARTS };
+struct DaRoute {
+    int form, gw;
+    bool by_e() const { return form != DA_RANGE; }
+};
+constexpr size_t DA_PARTS_BYTES = (size_t)64 << 20;  // largest partial sums [n][n][N_b] of a spin
+DaRoute dA_route(const DevSys& d, int n, int64_t W, int mode, bool det, int group);
 
 // Whether a call sorts the walkers of each electron index (Job.wperm), so
 // that a tile's survivors' union is tighter.  FP32 from the second tile on.
@@ -492,7 +500,7 @@ static_assert(offsetof(SlotRec64, pos) == 0 && offsetof(SlotRec64, f64) == 24 &&
               "slot record layout read by SlotR64::load");
 
 // Job lists of a call on one system: both spins in one launch per phase.
-constexpr int CALL_PHASES = 8;
+constexpr int CALL_PHASES = 9;
 constexpr size_t CALL_LIST_BYTES = (2 * sizeof(Job) + 5 * sizeof(int) + 255) / 256 * 256;
 constexpr size_t CALL_LISTS_BYTES = CALL_PHASES * CALL_LIST_BYTES;
 struct CallGrids {
@@ -533,18 +541,21 @@ struct WsLayout {
     size_t job_off;  // the device Job copy of per-system launches
     size_t call_off; // the CallLists of a forward or adjoint call
     size_t nwin_off[2], win_off[2], dA32_off[2], gnwin_off[2], gwin_off[2], gj_off[2], gs_off[2], g32_off[2];
+    size_t part_off[2];  // DA_PARTS: the electrons' partial sums
     size_t perm_off[2];  // walker order per electron, [n][W] int
+    DaRoute da[2];       // the adjoint's dA
     bool sorted;         // there is one
     size_t fwd_total;  // end of the forward's regions (tile lists, blocked-inversion copy)
     size_t total;      // end of the adjoint's regions
 };
-WsLayout ws_layout(const DevSys& d, int64_t W, int gw, int mode, bool by_e, bool sort = true);
+// (det, group: a plan's deterministic dA and adj_group)
+WsLayout ws_layout(const DevSys& d, int64_t W, int mode, bool sort = true, bool det = false, int group = 0);
 // The Job of spin s of a forward / adjoint call on workspace ws.
 // The FP32 products' default tile (per-system calls and a new plan): the
 // split-bf16 products, as accurate as FP32 MFMA and faster.
 constexpr int F32_TILE_DEFAULT = 2;
 Job fwd_job(qsl_system* sys, const qsl_fwd_args* a, const WsLayout& L, char* ws, int s, bool sorted = false);
-Job bwd_job(qsl_system* sys, const qsl_bwd_args* a, const WsLayout& L, char* ws, int s, int gw, bool by_e);
+Job bwd_job(qsl_system* sys, const qsl_bwd_args* a, const WsLayout& L, char* ws, int s);
 
 // ------------------------------------------------------------- launchers
 
@@ -660,9 +671,15 @@ void adj_dae_grid(Job& j);
 hipError_t launch_adj_dae(const Job& j, hipStream_t st);
 hipError_t launch_adj_dae_batched(int mode, int tile, const Job* jobs, const int* prefix, int njobs, int grid, hipStream_t st);
 hipError_t launch_finalize_dA(const float* dA32, double* dA, int64_t count, int accumulate, hipStream_t st);
-// dA = [dA +] sum_p part[p] (p ascending; float or double partials).
-hipError_t launch_reduce_dA(const void* part, bool fp64, int npart, int64_t count, double* dA, int accumulate,
-                            hipStream_t st);
+// dA = [dA +] sum_p part[p] (p ascending; float or double partials;
+// accumulate 1: onto dA one after the other, 2: the sum by itself first).
+struct ReduceDA {
+    const void* part;
+    double* dA;
+    int64_t count;
+    int npart, accumulate;
+};
+hipError_t launch_reduce_dA(bool fp64, const ReduceDA& a, const ReduceDA& b, hipStream_t st);  // one or (b.count) two
 hipError_t launch_build_mo(const DevSys& s, DevMO& mo, const double* A_dev, int64_t ld,
                            hipStream_t st);
 

@@ -84,22 +84,34 @@ hipError_t launch_finalize_dA(const float* dA32, double* dA, int64_t count, int 
 
 // dA (caller, FP64) = [dA +] sum over p = 0, 1, ... of the partial sums
 // part[p] (the deterministic dA: the same order on every call).
+// Eight partials' loads at a time are in flight.
 template <typename T>
-__global__ void reduce_dA_kernel(const T* __restrict__ part, int npart, int64_t count, double* __restrict__ dA,
-                                 int accumulate) {
+__global__ void reduce_dA_kernel(ReduceDA a, ReduceDA b) {
+    const ReduceDA& r = blockIdx.y ? b : a;
+    const T* __restrict__ part = (const T*)r.part;
+    double* __restrict__ dA = r.dA;
+    const int64_t count = r.count;
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < count; q += (int64_t)gridDim.x * blockDim.x) {
-        double acc = accumulate ? dA[q] : 0.0;
-        for (int p = 0; p < npart; ++p) acc += (double)part[(size_t)p * count + q];
-        dA[q] = acc;
+        double acc = r.accumulate == 1 ? dA[q] : 0.0;
+        int p = 0;
+        for (; p + 8 <= r.npart; p += 8) {
+            T v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = part[(size_t)(p + u) * count + q];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc += (double)v[u];
+        }
+        for (; p < r.npart; ++p) acc += (double)part[(size_t)p * count + q];
+        dA[q] = r.accumulate == 2 ? dA[q] + acc : acc;
     }
 }
 
-hipError_t launch_reduce_dA(const void* part, bool fp64, int npart, int64_t count, double* dA, int accumulate,
-                            hipStream_t st) {
-    if (count <= 0) return hipSuccess;
-    const int blocks = (int)std::min<int64_t>((count + 255) / 256, 8192);
-    if (fp64) reduce_dA_kernel<double><<<blocks, 256, 0, st>>>((const double*)part, npart, count, dA, accumulate);
-    else reduce_dA_kernel<float><<<blocks, 256, 0, st>>>((const float*)part, npart, count, dA, accumulate);
+hipError_t launch_reduce_dA(bool fp64, const ReduceDA& a, const ReduceDA& b, hipStream_t st) {
+    const int64_t most = std::max(a.count, b.count);
+    if (most <= 0) return hipSuccess;
+    const dim3 grid((unsigned)std::min<int64_t>((most + 255) / 256, 8192), b.count > 0 ? 2 : 1);
+    if (fp64) reduce_dA_kernel<double><<<grid, 256, 0, st>>>(a, b);
+    else reduce_dA_kernel<float><<<grid, 256, 0, st>>>(a, b);
     return hipGetLastError();
 }
 

@@ -169,7 +169,7 @@ struct MDLayout {
 // (group_max: at most so many determinants per group)
 static MDLayout md_layout(const DevSys& d, const DevMO mo[2], int64_t W, int mode, int n_det, int group_max = MD_GROUP_MAX) {
     MDLayout L{};
-    L.base = ws_layout(d, W, 1, mode, false, /*sort=*/false);  // the forward's part
+    L.base = ws_layout(d, W, mode, /*sort=*/false);  // the forward's part
     size_t off = L.base.fwd_total;
     const size_t cb = mode == QSL_FP64 ? 8 : 4;
     const int N = d.n_up + d.n_dn;

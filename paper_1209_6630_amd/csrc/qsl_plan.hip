@@ -65,7 +65,6 @@ struct qsl_plan {
     size_t ws_cap = 0;
     std::vector<size_t> ws_off;
     std::vector<WsLayout> lay;
-    std::vector<int> gw;
     // per-job (system, spin) Jobs and the device work lists of the phases
     std::vector<Job> fjobs, bjobs;
     PhaseList ph[PH_COUNT];
@@ -87,17 +86,6 @@ static void drop_graph(qsl_plan* p) {
     if (p->graph) hipGraphDestroy(p->graph);
     p->exec = nullptr;
     p->graph = nullptr;
-}
-
-// The plan's dA runs by electron (FP32 and FP64 without det_dA, systems whose
-// windows fit the slot screen's bitmap) or by 32-electron range.
-static bool plan_by_e(const qsl_plan* p, int i) {
-    return dA_by_electron(p->mode, p->tune.det_dA != 0) && p->sys[i]->d.n_win <= UNION_MAXWIN;
-}
-
-static int plan_gw(const qsl_plan* p, int i) {
-    const int64_t W = std::max<int64_t>(p->W[i], 1);
-    return p->tune.adj_group > 0 ? (int)std::min<int64_t>(p->tune.adj_group, W) : bw_group(W, plan_by_e(p, i));
 }
 
 // Jobs in falling order of n (the larger systems' blocks start first);
@@ -127,12 +115,10 @@ static qsl_status prepare(qsl_plan* p, hipStream_t st) {
     drop_graph(p);
     p->lay.resize(p->n_sys);
     p->ws_off.resize(p->n_sys);
-    p->gw.resize(p->n_sys);
     size_t total = 256;  // the item counter
     for (int i = 0; i < p->n_sys; ++i) {
-        p->gw[i] = plan_gw(p, i);
-        p->lay[i] = ws_layout(p->sys[i]->d, p->W[i], p->gw[i], p->mode, plan_by_e(p, i),
-                              /*sort=*/p->mode == QSL_FP32 || p->tune.det_dA == 0);
+        p->lay[i] = ws_layout(p->sys[i]->d, p->W[i], p->mode, /*sort=*/p->mode == QSL_FP32 || p->tune.det_dA == 0,
+                              p->tune.det_dA != 0, p->tune.adj_group);
         p->ws_off[i] = total;
         total = round_up(total + p->lay[i].total, 256);
     }
@@ -142,9 +128,9 @@ static qsl_status prepare(qsl_plan* p, hipStream_t st) {
     const size_t elem = p->mode == QSL_FP64 ? sizeof(double) : sizeof(float);
     for (int i = 0; i < p->n_sys && det; ++i) {
         if (!p->has_bwd[i]) continue;
-        const int64_t ngw = (p->W[i] + p->gw[i] - 1) / p->gw[i];
         for (int s = 0; s < 2; ++s) {
             if (!p->bwd[i].dA[s]) continue;
+            const int64_t gw = p->lay[i].da[s].gw, ngw = (p->W[i] + gw - 1) / gw;
             part_off[2 * i + s] = total;
             total = round_up(total + (size_t)ngw * n_spin(p->sys[i]->d, s) * p->sys[i]->d.n_basis * elem, 256);
         }
@@ -166,7 +152,7 @@ static qsl_status prepare(qsl_plan* p, hipStream_t st) {
             f.f32_tile = p->tune.contract_tile;
             p->fjobs.push_back(f);
             if (p->has_bwd[i]) {
-                Job b = bwd_job(p->sys[i], &p->bwd[i], p->lay[i], ws + p->ws_off[i], s, p->gw[i], plan_by_e(p, i));
+                Job b = bwd_job(p->sys[i], &p->bwd[i], p->lay[i], ws + p->ws_off[i], s);
                 b.f32_tile = p->tune.contract_tile;
                 if (det && part_off[2 * i + s] && (b.dA64 || b.dA32)) b.dApart = ws + part_off[2 * i + s];
                 p->bjobs.push_back(b);
@@ -342,9 +328,9 @@ static qsl_status enqueue(qsl_plan* p, hipStream_t st) {
             const Job& j = p->bjobs[k];
             const int64_t cnt = (int64_t)j.n * j.s.n_basis;
             if (j.dApart) {
-                const int64_t words = cnt * ((j.W + j.gw - 1) / j.gw) * (mode == QSL_FP64 ? 2 : 1);
+                const int64_t words = cnt * dA_parts(j) * (mode == QSL_FP64 ? 2 : 1);
                 if ((e = fill_u32((uint32_t*)j.dApart, 0u, words, st)) != hipSuccess) return hip_fail(e, "dA clear");
-                continue;
+                if (!j.by_e) continue;
             }
             if (j.dA32 && (e = fill_u32((uint32_t*)j.dA32, 0u, cnt, st)) != hipSuccess) return hip_fail(e, "dA clear");
             if (j.dA64 && !p->bwd[i].accumulate_dA && (e = fill_f64(j.dA64, 0.0, cnt, st)) != hipSuccess)
@@ -564,9 +550,9 @@ static qsl_status enqueue(qsl_plan* p, hipStream_t st) {
         for (int s = 0; s < 2; ++s, ++k) {
             const Job& j = p->bjobs[k];
             if (j.dApart && j.n) {
-                if ((e = launch_reduce_dA(j.dApart, mode == QSL_FP64, (int)((j.W + j.gw - 1) / j.gw),
-                                          (int64_t)j.n * j.s.n_basis, p->bwd[i].dA[s], p->bwd[i].accumulate_dA, st)) !=
-                    hipSuccess)
+                const ReduceDA r{j.dApart, p->bwd[i].dA[s], (int64_t)j.n * j.s.n_basis, dA_parts(j),
+                                 j.by_e ? 2 : p->bwd[i].accumulate_dA != 0};
+                if ((e = launch_reduce_dA(mode == QSL_FP64, r, ReduceDA{}, st)) != hipSuccess)
                     return hip_fail(e, "dA reduction");
                 continue;
             }
