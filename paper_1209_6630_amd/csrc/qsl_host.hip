@@ -127,11 +127,18 @@ ProfScope::~ProfScope() {
 // entry by range, so that they give the same bits every time.  By electron
 // they keep that by partial sums (22 electrons a spin, 128 walkers: by range
 // 1910 us, by electron 65 with atomics), as long as those are small.
+// FP64 with few walkers goes by range: by electron every electron pays for a
+// whole batch of 32 walkers whatever their number, by range the time follows
+// the walkers.  The line is where the two meet (us, by range against by
+// electron): 128 electrons a spin x 2 walkers 117 / 154, x 4 181 / 164; 217 x 1
+// 117 / 378, x 8 376 / 432, x 12 530 / 439; 866 x 1 913 / 8832, x 24 6104 /
+// 11584.
 DaRoute dA_route(const DevSys& d, int n, int64_t W, int mode, bool det, int group) {
     const auto gw = [&](int most) { return (int)std::min<int64_t>(std::max<int64_t>(W, 1), group > 0 ? group : most); };
     if (mode == QSL_BF16X3 || det || d.n_win > UNION_MAXWIN) return {DA_RANGE, gw(128)};
     if (mode == QSL_FP64 && n <= TE && W <= gw(128))
         return (size_t)n * n * d.n_basis * sizeof(double) <= DA_PARTS_BYTES ? DaRoute{DA_PARTS, gw(1024)} : DaRoute{DA_RANGE, gw(128)};
+    if (mode == QSL_FP64 && W * 4800 < (int64_t)n * n && W * 17 < n) return {DA_RANGE, gw(128)};
     return {DA_ELECTRON, gw(1024)};
 }
 
@@ -1062,9 +1069,20 @@ qsl_status qsl_backward(qsl_system* sys, const qsl_bwd_args* a, void* stream) {
         });
         if (e != hipSuccess) return hip_fail(e, split ? "G split kernel" : "G kernel");
     }
+    // Short blocks by range, of up to 32 walkers, run better with the Job as a
+    // kernel argument than read from a list: each spin by itself where it fills
+    // the chip (FP64, 866 electrons a spin x 1 walker 885 us, both in one launch
+    // 1086; 217 x 1, with 49 blocks a spin, 111 and 107).
+    const auto apart = [&](int ph, int s) { return ph == DA_R && P.job[s].gw <= 32 && P.blocks(ph, s) >= 256; };
     for (int ph : {DA_E, DA_R}) {
         if (!P.any(ph)) continue;
         ProfScope ps("adjoint_dA", st);
+        if (apart(ph, 0) || apart(ph, 1)) {
+            for (int s = 0; s < 2 && e == hipSuccess; ++s)
+                if (P.blocks(ph, s)) e = launch_adj_da(P.job[s], st);
+            if (e != hipSuccess) return hip_fail(e, "adjoint dA kernel");
+            continue;
+        }
         e = P.run(ph, [&](const Job* js, const int* pre, int nj, int nb) {
             return ph == DA_E ? launch_adj_dae_batched(a->mode, F32_TILE_DEFAULT, js, pre, nj, nb, st)
                               : launch_adj_da_batched(a->mode, js, pre, nj, nb, st);
