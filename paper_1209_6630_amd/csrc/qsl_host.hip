@@ -1046,9 +1046,30 @@ qsl_status qsl_backward(qsl_system* sys, const qsl_bwd_args* a, void* stream) {
         e = P.run(SCREEN, [&](const Job* js, const int* pre, int nj, int nb) { return launch_screen_batched(js, pre, nj, nb, 0, st); });
         if (e != hipSuccess) return hip_fail(e, "screen kernel");
     }
+    // Some blocks run better with the Job as a kernel argument than read from a
+    // list: then each spin by itself where it fills the chip.  By range, the
+    // short blocks of up to 32 walkers (FP64, 866 electrons a spin x 1 walker 885
+    // us, both in one launch 1086; 217 x 1, with 49 blocks a spin, 111 and 107).
+    // dR from H, all blocks (FP64, 866 x 128 16.8 ms and 17.9; 217 x 1024 5.0 and
+    // 5.1; FP32, 866 x 128 9.6 and 9.8, 866 x 16 2.58 and 2.53).  And where one
+    // spin alone has more threads than a launch of one dimension can.
+    const auto apart = [&](int ph) {
+        for (int s = 0; s < 2; ++s) {
+            const int64_t b = P.blocks(ph, s);
+            if (b >= (1ll << 32) / 512) return true;
+            if (ph == DA_R ? P.job[s].gw <= 32 && b >= 256 : ph == ADJ_H && b >= (a->mode == QSL_FP64 ? 1024 : 4096)) return true;
+        }
+        return false;
+    };
+    const auto one_by_one = [&](int ph, hipError_t (*launch)(const Job&, hipStream_t)) {
+        hipError_t r = hipSuccess;
+        for (int s = 0; s < 2 && r == hipSuccess; ++s)
+            if (P.blocks(ph, s)) r = launch(P.job[s], st);
+        return r;
+    };
     if (P.any(ADJ_H)) {
         ProfScope ps("adjoint_h", st);
-        e = P.run(ADJ_H, [&](const Job* js, const int* pre, int nj, int nb) { return launch_adj_h_batched(a->mode, js, pre, nj, nb, st); });
+        e = apart(ADJ_H) ? one_by_one(ADJ_H, launch_adj_h) : P.run(ADJ_H, [&](const Job* js, const int* pre, int nj, int nb) { return launch_adj_h_batched(a->mode, js, pre, nj, nb, st); });
         if (e != hipSuccess) return hip_fail(e, "adjoint H kernel");
     }
     if (P.any(SLOTS)) {
@@ -1069,21 +1090,10 @@ qsl_status qsl_backward(qsl_system* sys, const qsl_bwd_args* a, void* stream) {
         });
         if (e != hipSuccess) return hip_fail(e, split ? "G split kernel" : "G kernel");
     }
-    // Short blocks by range, of up to 32 walkers, run better with the Job as a
-    // kernel argument than read from a list: each spin by itself where it fills
-    // the chip (FP64, 866 electrons a spin x 1 walker 885 us, both in one launch
-    // 1086; 217 x 1, with 49 blocks a spin, 111 and 107).
-    const auto apart = [&](int ph, int s) { return ph == DA_R && P.job[s].gw <= 32 && P.blocks(ph, s) >= 256; };
     for (int ph : {DA_E, DA_R}) {
         if (!P.any(ph)) continue;
         ProfScope ps("adjoint_dA", st);
-        if (apart(ph, 0) || apart(ph, 1)) {
-            for (int s = 0; s < 2 && e == hipSuccess; ++s)
-                if (P.blocks(ph, s)) e = launch_adj_da(P.job[s], st);
-            if (e != hipSuccess) return hip_fail(e, "adjoint dA kernel");
-            continue;
-        }
-        e = P.run(ph, [&](const Job* js, const int* pre, int nj, int nb) {
+        e = apart(ph) ? one_by_one(ph, ph == DA_E ? launch_adj_dae : launch_adj_da) : P.run(ph, [&](const Job* js, const int* pre, int nj, int nb) {
             return ph == DA_E ? launch_adj_dae_batched(a->mode, F32_TILE_DEFAULT, js, pre, nj, nb, st)
                               : launch_adj_da_batched(a->mode, js, pre, nj, nb, st);
         });
