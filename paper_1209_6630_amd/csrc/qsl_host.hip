@@ -962,7 +962,7 @@ qsl_status qsl_backward(qsl_system* sys, const qsl_bwd_args* a, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     hipError_t e;
     const int N = d.n_up + d.n_dn;
-    const WsLayout L = ws_layout(d, a->W, a->mode);
+    const WsLayout L = ws_layout(d, a->W, a->mode, /*sort=*/a->mode != QSL_FP64);
     // the spins' partial sums are written to dA whole, unless both are to add to one
     const auto dA_bytes = [&](int s) { return (uintptr_t)n_spin(d, s) * d.n_basis * sizeof(double); };
     const bool dA_apart = (uintptr_t)a->dA[0] + dA_bytes(0) <= (uintptr_t)a->dA[1] || (uintptr_t)a->dA[1] + dA_bytes(1) <= (uintptr_t)a->dA[0];

@@ -454,16 +454,22 @@ struct DaRoute {
 constexpr size_t DA_PARTS_BYTES = (size_t)64 << 20;  // largest partial sums [n][n][N_b] of a spin
 DaRoute dA_route(const DevSys& d, int n, int64_t W, int mode, bool det, int group);
 
-// Whether a call sorts the walkers of each electron index (Job.wperm), so
-// that a tile's survivors' union is tighter.  FP32 from the second tile on.
-// FP64 where the products are long enough for the sort's launch to pay: the
-// sort takes 19 to 33 us and saves 4 to 9 % of the products (434 electrons x
+// Whether a forward or a plan sorts the walkers of each electron index
+// (Job.wperm), so that a tile's survivors' union is tighter.  FP32 from the
+// second tile on.  FP64 where the products are long enough for the sort to
+// pay: it takes 20 us at 1000 walkers, 90 from 4096 on, and saves 4 to 9 % of
+// the products, which grow with the square of the electrons (434 electrons x
 // 1024 walkers 9.38 -> 8.86 ms, 1731 x 96 11.45 -> 11.01, 158 x 1000 1.25 ->
-// 1.13); at 44 electrons x 64 walkers its launch alone would be 8 us of 70.
-// The FP64 outputs are the same either way (a slot that survives for other
-// walkers only adds zeros).
+// 1.13).  Whole forwards without and with it, us: 44 electrons x 1500 walkers
+// 295 / 327, 64 x 4096 1103 / 1144, 96 x 1400 799 / 807, 128 x 512 463 / 467,
+// 128 x 1024 888 / 883, 158 x 415 586 / 580, 256 x 256 910 / 894.  An FP64
+// adjoint by itself gains nothing from it (434 x 300 1081 / 1131).
+// The forward's FP64 outputs are the same either way (a slot that survives for
+// other walkers only adds zeros); dA's sums over walkers are regrouped.
 inline bool walker_sorted(const DevSys& d, int mode, int64_t W) {
-    return W > TE && (mode == QSL_FP32 || (mode == QSL_FP64 && (d.n_up + d.n_dn) * W >= 65536));
+    if (W <= TE || mode == QSL_BF16X3) return false;
+    const int64_t n = d.n_up, electrons = (d.n_up + d.n_dn) * W;  // (n_up >= n_dn)
+    return mode == QSL_FP32 || (n >= 64 && electrons >= 65536 && n * electrons >= 5000000);
 }
 
 // Workspace of one system: byte offsets of the per-spin tile and group
