@@ -99,9 +99,8 @@ struct GJShared {
     uint32_t ord[16][4];       // byte i / 16 of row i % 16: 1 + the step that took row i (0: none)
     int xready;                // last panel handed over to the panel wave
     int xfree;                 // last panel whose columns were taken from there
-    int bad;                   // 1: zero pivot, 2: non-finite pivot
-    int bad_panel;             // its panel (np: none so far)
-    int late;                  // a wave gave up waiting for the panel's columns to be taken back
+    int bad;                   // 1: zero pivot, 2: non-finite pivot (or a wait that gave up)
+    int bad_panel;             // the pivot's panel (np: none so far)
     // (the panel first: its addresses are constants within an LDS
     // instruction's offset)
     __device__ double* X() { return main; }
@@ -227,7 +226,7 @@ __device__ __forceinline__ int gjt_panel_careful(GJShared<NT>& S, int p, int n, 
 // the stages of the maximum stand between their updates.  A largest key
 // that is no ordinary number's is only noted; the panel is then done again.
 template <int NT>
-__device__ __forceinline__ void gjt_panels(const GJArgs& j, GJShared<NT>& S, int w, int lane) {
+__device__ __forceinline__ bool gjt_panels(const GJArgs& j, GJShared<NT>& S, int w, int lane) {
     using P = GJT<NT>;
     constexpr int RPL = P::RPL, LS = P::LS;
     constexpr bool EXACT = P::EXACT;
@@ -425,7 +424,7 @@ __device__ __forceinline__ void gjt_panels(const GJArgs& j, GJShared<NT>& S, int
             if (lane < 16) S.ord_of(S.perm[16 * p + lane]) = (uint8_t)(16 * p + lane + 1);
         }
         __syncthreads();
-        if (code) return;
+        if (code) return false;
         // the inversions that this panel's rows add to the permutation, lane
         // k < 16 those of step k (the smaller rows still open when it was
         // taken)
@@ -470,6 +469,7 @@ __device__ __forceinline__ void gjt_panels(const GJArgs& j, GJShared<NT>& S, int
         if (j.sign) j.sign[2 * (size_t)w + j.spin] = (neg & 1) ? -1 : 1;
         if (j.status && !isfinite(ld)) atomicOr(j.status + w, QSL_STATUS_NONFINITE);
     }
+    return true;
 }
 
 // Register tiles of an updating wave from C_1[e][i], the identity past n (so
@@ -640,7 +640,8 @@ __device__ __forceinline__ void gjt_update(const GJArgs& j, GJShared<NT>& S, int
                 }
             }
             if (pass == 0) {
-                if (!flag_wait(&S.xfree, p) && lane == 0) S.late = 1;
+                // (gave up: goes on to the same barriers, and all ends as NaN)
+                if (!flag_wait(&S.xfree, p) && lane == 0) S.bad = 2;
                 if (second) stage_tile(I1{}, p + 1);
                 else stage_tile(I0{}, p + 1);
                 __builtin_amdgcn_s_setprio(0);
@@ -648,7 +649,6 @@ __device__ __forceinline__ void gjt_update(const GJArgs& j, GJShared<NT>& S, int
         }
     }
     __syncthreads();  // the panels are no longer read
-    if (S.late) return;
     const uint4 o4 = *(const uint4*)S.ord[li];
     const uint32_t ov[4] = {o4.x, o4.y, o4.z, o4.w};
     auto step_of = [&](int ti) __attribute__((always_inline)) { return (int)((ov[ti >> 2] >> (8 * (ti & 3))) & 0xffu) - 1; };
@@ -693,19 +693,17 @@ __device__ __forceinline__ void gjt_body(const GJArgs& j, int w) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid < 64) ((uint32_t*)S.ord)[tid] = 0u;
-    if (tid == 0) { S.xready = S.xfree = -1; S.bad = S.late = 0; S.bad_panel = (j.n + 15) >> 4; }
+    if (tid == 0) { S.xready = S.xfree = -1; S.bad = 0; S.bad_panel = (j.n + 15) >> 4; }
     __syncthreads();
     if (wave == P::NU) {
-        gjt_panels<NT>(j, S, w, lane);
-        if (!S.bad) {
+        if (gjt_panels<NT>(j, S, w, lane)) {
             __syncthreads();
-            if (!S.late)
-                for (int q0 = 0; q0 < j.n; q0 += P::QC) gjt_copy_out<NT>(j, S, w, q0, wave, lane);
+            for (int q0 = 0; q0 < j.n; q0 += P::QC) gjt_copy_out<NT>(j, S, w, q0, wave, lane);
         }
     } else {
         gjt_update<NT>(j, S, w, wave, lane);
     }
-    if (S.bad || S.late) {
+    if (S.bad) {
         // undefined inverse: NaN, sign = 0, log|det| = -inf (a zero pivot) or NaN
         const size_t nn = (size_t)j.n * j.n;
         double* Dw = j.Dinv + (size_t)w * nn;
