@@ -35,7 +35,10 @@
 //
 // Bound: the panel wave's chain of search, reciprocal and update (about 800
 // cycles a step at n = 79, 1200 at n = 217), then the rank-16 updates at the
-// FP64 matrix rate (the same as the vector rate here).  Measured, against the
+// FP64 matrix rate (the same as the vector rate here).  A matrix of up to 16
+// takes its own n steps only, not the identity's: 65536 of n = 1 in 126 us (321
+// with all 16 steps, 131 by rank-1 steps), 60000 of n = 5 in 208 (298, 284),
+// 8192 of n = 8 in 42 (50, 78).  Measured, against the
 // eight waves that published one or two rank-1 steps at a time through LDS
 // before: one matrix of n = 79 in 53 us (162), 2048 of them in 205 us (775),
 // 777 of n = 132 in 479 us (741), 2048 of n = 217 in 2.30 ms (2.61).
@@ -236,10 +239,17 @@ __device__ __forceinline__ bool gjt_panels(const GJArgs& j, GJShared<NT>& S, int
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
         const int row = lane + 64 * r;
-        open[r] = __ballot(row < 16 * np);
+        open[r] = __ballot(row < (NT == 1 ? n : 16 * np));
         mine[r] = row < P::NP ? row : P::NP + (lane & 7);
     }
     int inversions = 0;  // of the pivot permutation, by lanes
+    if constexpr (NT == 1) {  // the identity's steps past n, which are not taken
+        for (int k = n; k < 16; ++k) S.F(0)[k * LS + mine[0]] = 0.0;
+        if (lane >= n && lane < 16) {
+            S.pvs[lane] = 1.0;
+            S.perm[lane] = lane;
+        }
+    }
     __builtin_amdgcn_s_setprio(3);
 #pragma unroll 1
     for (int p = 0; p < np; ++p) {
@@ -272,6 +282,7 @@ __device__ __forceinline__ bool gjt_panels(const GJArgs& j, GJShared<NT>& S, int
         static_for<0, 6>([&](auto sc) __attribute__((always_inline)) { key = umax_stage<decltype(sc)::value>(key); });
         static_for<0, 16>([&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
+            if (NT == 1 && k >= n) return;  // (a whole panel of a tiny matrix is mostly identity)
             const uint32_t sk = (uint32_t)__builtin_amdgcn_readlane((int)key, 63);
             odd |= gj_odd<EXACT>(sk);
             uint64_t m[RPL];  // the pivot's lane
@@ -438,7 +449,7 @@ __device__ __forceinline__ bool gjt_panels(const GJArgs& j, GJShared<NT>& S, int
             }
 #pragma unroll
             for (int k = 0; k < 16; ++k) below -= k < lane && __builtin_amdgcn_readlane(row, k) < row;
-            inversions += lane < 16 ? below : 0;
+            inversions += lane < (NT == 1 ? n : 16) ? below : 0;
         }
     }
     __builtin_amdgcn_s_setprio(0);
@@ -566,6 +577,7 @@ __device__ __forceinline__ void gjt_update(const GJArgs& j, GJShared<NT>& S, int
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
             if (lane == 0) flag_store(&S.xfree, p);
         }
+        if (NT == 1 && n == 1) break;  // no further step
         // the pivot rows' entries of this wave's columns
         {
             const uint4 o4 = *(const uint4*)S.ord[li];

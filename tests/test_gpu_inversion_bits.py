@@ -45,7 +45,7 @@ def _eliminate(D):
     return X, np.array(piv)
 
 
-@pytest.mark.parametrize("n", [1, 7, 16, 17, 33, 63, 65, 80])
+@pytest.mark.parametrize("n", [1, 2, 3, 7, 8, 15, 16, 17, 33, 63, 65, 80])
 def test_rank_one_steps_bit_for_bit(n):
     print(f"[case] inversion bits n={n}", flush=True)
     sysm, A_up, A_dn = random_tiny(n_atoms=n // 3 + 2, n_up=n, n_dn=1, seed=n + 40)
