@@ -634,10 +634,9 @@ hipError_t launch_gj(const Job& j, hipStream_t st);
 hipError_t launch_gj_batched(int v, const Job* jobs, const int* prefix, int njobs, int grid, hipStream_t st);
 // Row length of the FP32 G of the dA by electron: whole blocks of 224 MOs, or
 // of 32 where one workgroup takes all.
-__host__ __device__ inline int g32_ld(int n) {
-    const int b = n <= ADJ_MB ? 32 : ADJ_MB;
-    return (n + b - 1) / b * b;
-}
+// (Constant divisors: by a variable one, the dA kernel computed its rows'
+// addresses in vector registers, 5.94 ms instead of 5.83 at 434 electrons x 4096.)
+__host__ __device__ inline int g32_ld(int n) { return n <= ADJ_MB ? (n + 31) & ~31 : (n + ADJ_MB - 1) / ADJ_MB * ADJ_MB; }
 // G = g D^-1 in FP32 (Job.g32) for walkers bound without the epilogue.
 int g32_blocks(const Job& j);
 hipError_t launch_g32(const Job& j, hipStream_t st);
