@@ -170,17 +170,7 @@ __device__ __forceinline__ int gjt_panel_careful(GJShared<NT>& S, int p, int n, 
     const int n16 = (n + 15) & ~15;
     double *X = S.X(), *F = S.F(p);
 #pragma unroll 1
-    for (int k = 0; k < 16; ++k) {
-        if (16 * p + k >= n) {
-            if (lane == 0) {
-                S.pvs[16 * p + k] = 1.0;
-                S.perm[16 * p + k] = 16 * p + k;
-                S.ord_of(16 * p + k) = (uint8_t)(16 * p + k + 1);
-            }
-#pragma unroll 1
-            for (int row = lane; row < P::NP; row += 64) F[k * LS + row] = 0.0;
-            continue;
-        }
+    for (int k = 0; k < min(16, n - 16 * p); ++k) {
         uint64_t best = 0;  // |x| and 255 - i, or the key, to be largest
         int at = 0;
 #pragma unroll 1
@@ -217,6 +207,13 @@ __device__ __forceinline__ int gjt_panel_careful(GJShared<NT>& S, int p, int n, 
             X[k * LS + row] = fma(f, pv + 1.0, x);
         }
     }
+    if (16 * p + lane >= n && lane < 16) {
+        S.pvs[16 * p + lane] = 1.0;
+        S.perm[16 * p + lane] = 16 * p + lane;
+        S.ord_of(16 * p + lane) = (uint8_t)(16 * p + lane + 1);
+    }
+#pragma unroll 1
+    for (int q = max(n - 16 * p, 0) * LS + lane; q < 16 * LS; q += 64) F[q] = 0.0;
     return 0;
 }
 
