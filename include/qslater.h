@@ -336,9 +336,10 @@ qsl_status qsl_plan_destroy(qsl_plan* plan);
  * tuning (logdet, sign, D^-1, drift, Laplacian and dR of the first and last
  * walkers of every system within 1e-9 relative, dA within 1e-10 (FP64) or
  * 1e-4 (other modes) of its largest entry), and set it on the plan.  With
- * cache_path, a JSON file keyed by device, mode and the shapes of the
- * batch: a hit sets the cached tuning without running anything; a miss
- * tunes and writes the entry.  Overwrites the bound outputs, dA included:
+ * cache_path, a JSON file keyed by device, kernel version, mode and the
+ * shapes of the batch: a hit sets the cached tuning without running
+ * anything; a miss (an entry of other kernels among them) tunes and writes
+ * the entry.  Overwrites the bound outputs, dA included:
  * while tuning, every run writes dA as if accumulate_dA were 0 (the
  * caller's flags apply again to later launches), so an accumulated dA must
  * be saved by the caller first.  Synchronises `stream`.  `chosen` (may be

@@ -599,12 +599,17 @@ static qsl_status launch_plan(qsl_plan* p, hipStream_t st) {
 
 // ------------------------------------------------------------- autotuner
 
+// Raised whenever a tuning value comes to mean another kernel or shape (gj_bias:
+// the inversion's shapes; adj_group: the form of the FP64 dA): an entry
+// measured on other kernels is tuned again, not applied.
+constexpr int TUNE_VERSION = 2;
+
 static std::string tune_key(const qsl_plan* p) {
     hipDeviceProp_t prop{};
     std::string arch = "unknown";
     if (hipGetDeviceProperties(&prop, p->device) == hipSuccess) arch = prop.gcnArchName;
     std::ostringstream k;
-    k << arch << "|mode" << p->mode;
+    k << arch << "|kernels" << TUNE_VERSION << "|mode" << p->mode;
     for (int i = 0; i < p->n_sys; ++i) {
         const DevSys& d = p->sys[i]->d;
         k << "|" << d.n_up << "x" << d.n_dn << "b" << d.n_basis << "a" << d.n_atoms << "w" << p->W[i]
