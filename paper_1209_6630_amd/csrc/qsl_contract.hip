@@ -617,7 +617,6 @@ __device__ __forceinline__ void contract_f64_body(const Job& j, int bx, int by, 
     __shared__ double epos[TE][3];
     __shared__ double B[5 * TE * LD];
     __shared__ int ring[F32_RING];
-    __shared__ int ringo[F32_RING];  // slot * ldn: the slot's coefficient row
     __shared__ uint32_t wmask[F32_BATCH];
     __shared__ int s_tail;
     __shared__ int wt[TE];  // the tile's walkers (Job.wperm order)
@@ -701,9 +700,7 @@ __device__ __forceinline__ void contract_f64_body(const Job& j, int bx, int by, 
             }
             int pos = tail + x - c;
             for (uint32_t mm = m; mm; mm &= mm - 1) {
-                const int sl = q * WIN + __builtin_ctz(mm);
-                ring[pos & (F32_RING - 1)] = sl;
-                ringo[pos & (F32_RING - 1)] = sl * ldn;
+                ring[pos & (F32_RING - 1)] = q * WIN + __builtin_ctz(mm);
                 ++pos;
             }
             if (lane == F32_BATCH - 1) s_tail = tail + x;
@@ -717,9 +714,9 @@ __device__ __forceinline__ void contract_f64_body(const Job& j, int bx, int by, 
         const int kk = tid & (KC - 1), eg = tid / KC;
         const bool live = head + kk < tail;
         const int slot = live ? ring[(head + kk) & (F32_RING - 1)] : 0;
-        // the last chunk: entries past the list become row 0 (the filter is
+        // the last chunk: entries past the list become slot 0 (the filter is
         // done, nothing is appended after); their values are zero
-        if (!live && eg == 0) ringo[(head + kk) & (F32_RING - 1)] = 0;
+        if (!live && eg == 0) ring[(head + kk) & (F32_RING - 1)] = 0;
         SlotR64 r;
         r.load(srec64 + slot);
 #pragma unroll 1
@@ -745,7 +742,8 @@ __device__ __forceinline__ void contract_f64_body(const Job& j, int bx, int by, 
         double bn[UMAX], an[5];
         const double* Bh = B + (16 * half + li) * LD + lg;
         auto load = [&](int t) __attribute__((always_inline)) {
-            const int row = ringo[(head + 4 * t + lg) & (F32_RING - 1)];
+            // the slot's coefficient row (its offset may pass 2^31)
+            const int64_t row = (int64_t)ring[(head + 4 * t + lg) & (F32_RING - 1)] * ldn;
 #pragma unroll
             for (int q = 0; q < UMAX; ++q) bn[q] = gmem(Aw)[row + boff[q]];
 #pragma unroll
