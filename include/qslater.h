@@ -137,8 +137,9 @@ qsl_status qsl_set_mo(qsl_system* sys, int32_t spin, const double* A, int64_t ld
                       int32_t on_device, void* stream);
 
 /* Forward arguments.  Output pointers are device memory.  C and Dinv are
- * required (the inversion reads C_1, the drift reads Dinv); logdet, sign,
- * drift, lap and status may be NULL to skip them. */
+ * required (the inversion reads C_1, the drift reads Dinv); a caller that
+ * needs neither may give one buffer for both spins (they then run one after
+ * the other).  logdet, sign, drift, lap and status may be NULL to skip them. */
 typedef struct {
     int64_t W;                /* walkers                                        */
     const double* R;          /* [W][n_up+n_dn][3] device, bohr                  */
@@ -192,9 +193,11 @@ qsl_status qsl_forward(qsl_system* sys, const qsl_fwd_args* args, void* stream);
  * in the array needs to start at zero (each call writes what it reads).
  * Outputs equal those of qsl_forward bit for bit.
  * Errors: those of qsl_forward; WORKSPACE when the forward of args->W walkers
- * needs more than QSL_NOALLOC_SCRATCH_BYTES (qsl_workspace_size with
- * QSL_WS_FORWARD gives the need: about 43 MB for 4096 walkers of 434
- * electrons); HIP if the array's device address cannot be found.
+ * does not fit: a need of up to QSL_NOALLOC_SCRATCH_BYTES by
+ * qsl_workspace_size with QSL_WS_FORWARD (about 43 MB for 4096 walkers of 434
+ * electrons) always does, and somewhat more may (the call's job lists have
+ * room of their own, and FP64 goes without its walker order where only that
+ * fits); HIP if the array's device address cannot be found.
  */
 #define QSL_NOALLOC_SCRATCH_BYTES (64u << 20)
 qsl_status qsl_forward_noalloc(qsl_system* sys, const qsl_fwd_args* args, void* stream);
@@ -217,12 +220,15 @@ typedef struct {
 
 /*
  * Backward: recomputes the AO values (never stored by the forward) and
- * accumulates dA = sum_w G chi over walkers, G = g D^-1: in FP32 by
+ * accumulates dA = sum_w G chi over walkers, G = g D^-1: in FP32 and FP64 by
  * electron index (per electron and group of up to 1024 walkers, the slots
  * that survive for some walker of the group, the walkers as the products'
- * contraction dimension), in the other modes by ranges of 32 electrons over
- * groups of up to 128 walkers; sums across groups are FP32 (FP64 in FP64
- * mode) atomic adds, then added to dA in FP64.  dR: with drift
+ * contraction dimension), in split BF16, and in FP64 with few walkers of many
+ * electrons, by ranges of 32 electrons over groups of up to 128 walkers; sums
+ * across electrons or ranges and groups are FP32 (FP64 in FP64 mode) atomic
+ * adds, which may round in any order, then added to dA in FP64.  An FP64 spin
+ * of up to 32 electrons with up to 128 walkers is summed in a fixed order
+ * instead: the same dA on every call.  dR: with drift
  * given, dR[w][e] = g[w][s(e)] drift[w][e] (0 where g = 0), since
  * d log|det D^s| / dr_e = sum_i D^-1[e][i] grad phi_i(r_e) is the drift
  * ("vector products" equations); without it, G A at the recomputed AO
@@ -257,8 +263,8 @@ typedef struct {
     int32_t batched;    /* 1: one launch per phase over the work list of all
                            systems; 0: one launch per system and spin       */
     int32_t adj_group;  /* walkers per dA group of the adjoint, 1..4096;
-                           0: min(W, 1024) for the dA by electron (FP32, FP64),
-                           min(W, 128) for the dA by 32-electron range     */
+                           0: min(W, 1024) for the dA by electron, min(W, 128)
+                           for the dA by 32-electron range (qsl_backward)    */
     int32_t gj_bias;    /* 0: the smallest Gauss-Jordan block shape holding
                            n; 1: the next larger one (when there is one)      */
     int32_t contract_tile; /* FP32 products: 0 = 256 MOs per workgroup, two
@@ -315,8 +321,10 @@ qsl_status qsl_plan_get_tuning(const qsl_plan* plan, qsl_tuning* t);
  * Enqueue the forward of every system, then the adjoint of every system
  * bound with `bwd`, on `stream`.  Results equal those of qsl_forward /
  * qsl_backward per system with the same tuning (bit for bit, except dA,
- * whose atomic sums over walker groups may round in any order; with
- * det_dA = 1, dA too is the same on every launch).  The first
+ * whose atomic sums over electrons and walker groups may round in any order;
+ * with det_dA = 1, and for an FP64 spin of up to 32 electrons with one walker
+ * group of up to adj_group (0: 128) walkers, dA too is the same on every
+ * launch).  The first
  * launch after a bind or a tuning change synchronises `stream`, uploads the
  * work lists and (QSL_PLAN_GRAPH) captures the graph; later launches only
  * enqueue.  Launches of one plan must not overlap.
@@ -387,6 +395,7 @@ typedef struct {
     size_t ws_bytes;
 } qsl_multidet_args;
 
+/* A workspace of that size also serves fewer walkers and determinants. */
 qsl_status qsl_multidet_workspace_size(const qsl_system* sys, int64_t W, int32_t mode, int32_t n_det, size_t* bytes);
 
 /*

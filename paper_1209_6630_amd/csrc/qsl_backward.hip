@@ -1154,7 +1154,8 @@ __device__ __forceinline__ void adj_dae_s3_body(const Job& j, int bx, int by) {
 // Bound by FP64 issue (the values' exponentials and the products share the
 // unit): 434 electrons x 1024 walkers 3.7 ms, by 32-electron range, which
 // evaluates 3.6x the group's slots, 8.0 ms; groups of 512 or 256 walkers 3.5
-// and 3.6 ms.
+// and 3.6 ms.  (dA_route: few walkers of many electrons go by range; small calls
+// add into partial sums, one per electron.)
 constexpr int DF_NS = 64;   // slots per chunk (four waves x 16)
 constexpr int DF_MT = ADJ_MB / 16;
 constexpr int DF_LD = ADJ_MB + 16;

@@ -550,7 +550,9 @@ __device__ __forceinline__ void contract_f32_body(const Job& j, int bx, int by, 
 // Measured, before and now: 434 electrons x 1024 walkers 20.3 and 9.5 ms (the
 // products alone 6.9, 4.9 at the matrix rate; the evaluation 2.6), 1731 x 96
 // 21.1 and 11.6 ms, 158 x 1000 2.45 and 1.25 ms.  Without gain: two chunk
-// buffers, evaluating the next chunk beside the products (10.3 ms: it spills).
+// buffers, evaluating the next chunk beside the products (10.3 ms: it spills
+// more; as it is, both shapes keep 44 and 42 registers in scratch, 116 and 108
+// bytes a lane).
 template <int NW>
 struct F64T {
     static constexpr int UMAX = 4;                      // MO blocks per wave

@@ -57,7 +57,10 @@ struct GJT {
     static constexpr int CT = 2;                    // D column tiles per updating wave
     static constexpr int NU = (NT + CT - 1) / CT;   // updating waves
     static constexpr int THREADS = (NU + 1) * 64;   // and the panel wave
-    static constexpr int WPE = NT <= 4 ? 4 : NT <= 9 ? 3 : 2;  // waves per SIMD
+    // waves per SIMD asked of the compiler; its registers allow 4 up to NT = 3,
+    // 2 at 4, 3 at 5, 7 and 8 (5 to 13 spilled), 1 at 6, 2 from 9 on (76 and 119
+    // spilled at 13 and 14: 260 and 288 bytes a lane)
+    static constexpr int WPE = NT <= 4 ? 4 : NT <= 9 ? 3 : 2;
     static constexpr int NP = 16 * NT;
     static constexpr int RPL = (NP + 63) / 64;      // panel rows per lane
     static constexpr bool EXACT = NT <= GJ_V_APPROX;  // pivot by the full |a| (else to 2^-12)

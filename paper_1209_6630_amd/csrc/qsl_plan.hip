@@ -33,7 +33,7 @@ enum Phase {
     PH_SLOTS_G,      // dA by electron: the (electron, walker group) slot lists
     PH_G32,          // dA by electron: G = g D^-1 in FP32 where no epilogue writes it
     PH_ADJ_DAE,      // dA by electron
-    PH_SORT,         // walker order per electron index (FP32 with the dA by electron; runs first)
+    PH_SORT,         // walker order per electron index (walker_sorted; runs first)
     PH_COUNT
 };
 
@@ -455,7 +455,7 @@ static qsl_status enqueue(qsl_plan* p, hipStream_t st) {
         // the adjoint's walker-group lists: the union of the forward's tile
         // lists (same positions), or a screening of their own for systems
         // with more windows than the union bitmap holds
-        // (tiles in a walker order of their own (FP32) cannot give the
+        // (tiles in a walker order of their own cannot give the
         // unions of consecutive walkers: those groups are screened directly)
         bool small = true;
         for (const Job& j : SG.jobs) small = small && j.s.n_win <= UNION_MAXWIN && !j.wperm;
