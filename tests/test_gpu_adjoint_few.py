@@ -60,3 +60,62 @@ def test_one_walker_of_many_electrons_is_quick():
         return best
 
     assert time(1) * 3 <= time(64)
+
+
+def _plan(S, Rt, gt, group, dR, dA):
+    from paper_1209_6630_amd.api import Plan
+    W = Rt.shape[0]
+    P = Plan([S], [W], "fp64", graph=False)
+    P.tuning = dict(batched=1, adj_group=group)
+    out = S.alloc_outputs(W, "fp64")
+    P.bind(0, Rt, out, g=gt, dR=dR, dA=dA)
+    P.launch()
+    return P, out
+
+
+@pytest.mark.parametrize("n_up,n_dn,W,group", [(40, 39, 47, 1), (40, 30, 90, 8), (40, 17, 90, 40), (129, 20, 13, 5)])
+def test_small_groups_of_a_plan(n_up, n_dn, W, group):
+    import torch
+    print(f"[case] fp64 dA small groups n={n_up}/{n_dn} W={W} group={group}", flush=True)
+    sysm, A_up, A_dn = random_tiny(n_atoms=(n_up + n_dn) // 8 + 2, n_up=n_up, n_dn=n_dn, seed=n_up + W)
+    R = walkers_near(sysm, W, seed=n_up)
+    g = np.random.default_rng(W).normal(size=(W, 2))
+    S = make_gpu_system(sysm, A_up, A_dn)
+    Rt, gt = torch.from_numpy(R).cuda(), torch.from_numpy(g).cuda()
+    dR = torch.empty_like(Rt)
+    dA = tuple(torch.empty((n, S.n_basis), dtype=torch.float64, device="cuda") for n in (n_up, n_dn))
+    P, out = _plan(S, Rt, gt, group, dR, dA)
+    ref = {k: out[k].cpu().numpy() for k in ("Dinv_up", "Dinv_dn")}
+    rdR, rdAu, rdAd = oracle.backward(sysm, A_up, A_dn, R, ref["Dinv_up"], ref["Dinv_dn"], g)
+    bA, bR = _abs_bounds(sysm, A_up, A_dn, R, ref, g)
+    for got, want, b in ((dA[0], rdAu, bA[0]), (dA[1], rdAd, bA[1]), (dR, rdR, bR)):
+        assert np.all(np.abs(got.cpu().numpy() - want) <= 1e-10 * b + 1e-300)
+
+
+def test_groups_of_one_walker_are_no_batches_of_32():
+    """dA of 512 walkers of 79 electrons a spin in groups of one: by range 3.3
+    times the time of groups of 32, by electron 29 times; at most 8 allowed."""
+    import torch
+    from paper_1209_6630_amd import _lib
+    import qsl_synth as q
+    print("[case] fp64 dA in groups of one walker", flush=True)
+    sysm, A_up, A_dn, R = q.make_config("158e", W=512)
+    S = make_gpu_system(sysm, A_up, A_dn)
+    Rt = torch.from_numpy(R).cuda()
+    gt = torch.ones((512, 2), dtype=torch.float64, device="cuda")
+    dR = torch.empty_like(Rt)
+    dA = tuple(torch.empty((n, S.n_basis), dtype=torch.float64, device="cuda") for n in (sysm.n_up, sysm.n_dn))
+
+    def ms(group):
+        P, _ = _plan(S, Rt, gt, group, dR, dA)
+        torch.cuda.synchronize()
+        _lib.profile_enable(True)
+        try:
+            _lib.profile_read()
+            for _ in range(5):
+                P.launch()
+            return _lib.profile_read()["adjoint_dA"][1] / 5
+        finally:
+            _lib.profile_enable(False)
+
+    assert ms(1) <= 8 * ms(32)
