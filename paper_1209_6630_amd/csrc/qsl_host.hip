@@ -135,11 +135,14 @@ ProfScope::~ProfScope() {
 // 11584.
 // So do several small groups (a plan's adj_group): by electron every electron
 // of every group pays for that batch and for a flush, groups n^2 of them; by
-// range a group's time follows its walkers (without a walker order, us).  79
-// electrons a spin x 512 walkers in groups of 1 2146 / 23104, of 16 681 / 1508,
-// of 32 655 / 781, of 40 794 / 665; 217 x 256 of 48 2016 / 2627, of 64 1780 / 1822;
-// 128 x 256 of 40 891 / 974, of 48 1018 / 855; 22 x 512 of 8 93 / 290, 22 x 256
-// of 16 142 / 93; 79 x 64 of 8 125 / 374, of 32 356 / 115.
+// range a group's time follows its walkers.  79 electrons a spin x 512 walkers
+// in groups of 1 2143 / 23104, of 16 761 / 1508, of 32 818 / 781, of 40 998 /
+// 665; 128 x 256 of 32 911 / 1078, of 40 1093 / 974; 217 x 256 of 48 2266 / 2627,
+// of 56 2442 / 2220; 22 x 512 of 8 93 / 290, 22 x 256 of 16 142 / 93; 79 x 64
+// of 8 125 / 374, of 32 356 / 115.  (Groups of ordered walkers are screened
+// directly; without an order, 79 x 512 in groups of 32 take 655, but the products
+// more: whole plans of 79 x 512 to 866 x 128 in groups of 1 to 48 take 0.89 to
+// 1.07 times as long without it.)
 DaRoute dA_route(const DevSys& d, int n, int64_t W, int mode, bool det, int group) {
     const auto gw = [&](int most) { return (int)std::min<int64_t>(std::max<int64_t>(W, 1), group > 0 ? group : most); };
     if (mode == QSL_BF16X3 || det || d.n_win > UNION_MAXWIN) return {DA_RANGE, gw(128)};
@@ -147,7 +150,7 @@ DaRoute dA_route(const DevSys& d, int n, int64_t W, int mode, bool det, int grou
         return (size_t)n * n * d.n_basis * sizeof(double) <= DA_PARTS_BYTES ? DaRoute{DA_PARTS, gw(1024)} : DaRoute{DA_RANGE, gw(128)};
     if (mode == QSL_FP64 && W * 4800 < (int64_t)n * n && W * 17 < n) return {DA_RANGE, gw(128)};
     const int64_t g = gw(1024), groups = (W + g - 1) / g;
-    if (mode == QSL_FP64 && groups > 1 && g <= std::min(56, 24 + n / 8) && groups * n * n > 1450 * g + 1000) return {DA_RANGE, gw(128)};
+    if (mode == QSL_FP64 && groups > 1 && g <= std::min(56, 22 + n / 8) && groups * n * n > 1450 * g + 1000) return {DA_RANGE, gw(128)};
     return {DA_ELECTRON, (int)g};
 }
 
